@@ -70,6 +70,9 @@ constexpr int kMaxLog2Single64 = 13;   // and 8192 points (FP64)
 // 32 values, exchanges through LDS in two halves), 8192 in FP64.
 constexpr int kMaxLog2Rows32 = 15;
 constexpr int kMaxLog2Rows64 = 13;
+// Overlap-save chirp-z rows: two workgroups per CU (at four waves per SIMD).
+constexpr int kMaxLog2Os32 = 13;
+constexpr int kMaxLog2Os64 = 12;
 // Values per thread of the second four-step pass of the spectrum and
 // synthesis transforms (its twiddle table, d_tw_n1, is built for it).
 constexpr int kPass2E = 8;
@@ -138,8 +141,12 @@ struct qtam_plan_s {
   void* d_tw_dn2 = nullptr;
   bool bluestein = false;       // N_out not a power of two: chirp-z rows of length bs_len
   int64_t bs_len = 0;
+  bool bs_os = false;           // chirp-z rows by overlap-save blocks of length bs_len (plain windows)
+  OsPlan os{};                  // their geometry (device pointer in os.blocks)
+  std::vector<int> os_blocks;   // [R] host copy of os.blocks
   void* d_bs_chirp = nullptr;   // [N_out] e^{+pi i v^2 / N_out}
-  void* d_bs_bf = nullptr;      // [bs_len] FFT of the wrapped conjugate chirp / bs_len (forward rows)
+  void* d_bs_bf = nullptr;      // [bs_len] FFT of the wrapped conjugate chirp / bs_len (forward rows);
+                                // overlap-save rows: [os.nmax * bs_len], one per block, both directions
   void* d_bs_bi = nullptr;      // [bs_len] FFT of the wrapped chirp / bs_len (inverse rows)
   void* d_bs_tw = nullptr;      // Stockham twiddles of bs_len
   int radix_r = 1;              // N/2 = radix_r * m2
@@ -335,8 +342,33 @@ qtam_status upload(qtam_plan_s* pl) {
     twiddles_strided(tw, ncs, nf, lr);
     o_rc = blob.add(tw.data(), tw.size() * sizeof(T));
   }
-  size_t o_bsc = 0, o_bsf = 0, o_bsi = 0, o_bstw = 0;
-  if (pl->bluestein) {
+  size_t o_bsc = 0, o_bsf = 0, o_bsi = 0, o_bstw = 0, o_osb = 0;
+  if (pl->bs_os) {
+    const int64_t M = hp.n_out, Lb = pl->bs_len;
+    auto chirp = [&](int64_t v) {   // e^{+pi i v^2 / M}, v^2 reduced mod 2M exactly
+      return std::polar(1.0, M_PI * static_cast<double>((v * v) % (2 * M)) / static_cast<double>(M));
+    };
+    std::vector<T> ta(2 * M), tb(2 * size_t(pl->os.nmax) * size_t(Lb));
+    for (int64_t v = 0; v < M; ++v) {
+      const std::complex<double> a = chirp(v);
+      ta[2 * v] = static_cast<T>(a.real());
+      ta[2 * v + 1] = static_cast<T>(a.imag());
+    }
+    std::vector<std::complex<double>> seg(Lb);
+    for (int64_t i = 0; i < pl->os.nmax; ++i) {   // lags V_i .. V_i + L - 1
+      for (int64_t u = 0; u < Lb; ++u) seg[u] = std::conj(chirp(i * pl->os.B - pl->os.JP + u));
+      host_fft(seg);
+      for (int64_t k = 0; k < Lb; ++k) {
+        tb[2 * (i * Lb + k)] = static_cast<T>(seg[k].real() / static_cast<double>(Lb));
+        tb[2 * (i * Lb + k) + 1] = static_cast<T>(seg[k].imag() / static_cast<double>(Lb));
+      }
+    }
+    o_bsc = blob.add(ta.data(), ta.size() * sizeof(T));
+    o_bsf = blob.add(tb.data(), tb.size() * sizeof(T));
+    stockham_twiddles(tw, Lb, engine_e(Lb, f64), TW_MIXED);
+    o_bstw = blob.add(tw.data(), tw.size() * sizeof(T));
+    o_osb = blob.add(pl->os_blocks.data(), pl->os_blocks.size() * sizeof(int));
+  } else if (pl->bluestein) {
     const int64_t M = hp.n_out, Lb = pl->bs_len;
     std::vector<std::complex<double>> a(M), bf(Lb), bi(Lb);
     for (int64_t v = 0; v < M; ++v) {
@@ -419,6 +451,10 @@ qtam_status upload(qtam_plan_s* pl) {
     pl->d_bs_bf = d + o_bsf;
     pl->d_bs_bi = d + o_bsi;
     pl->d_bs_tw = pl->bs_long ? nullptr : d + o_bstw;
+    if (pl->bs_os) {
+      pl->d_bs_bi = nullptr;
+      pl->os.blocks = reinterpret_cast<const int*>(d + o_osb);
+    }
   }
   pl->d_tw_half = pl->four_step ? nullptr : d + o_half;
   pl->d_tw_n1 = pl->four_step ? d + o_n1 : nullptr;
@@ -661,6 +697,38 @@ bool launch_rows_bs(bool forward, int log2l, const void* in, void* out, const Ro
                            static_cast<const C*>(in), static_cast<C*>(out), rows, static_cast<const T*>(tab), \
                            R, int(total_rows), int(sum_len), M, static_cast<const C*>(chirp),          \
                            static_cast<const C*>(bhat), static_cast<const C*>(tw));                    \
+      return true;                                                                                     \
+    }                                                                                                  \
+    return false;
+    QTAM_POW2_CASES(X)
+#undef X
+    default: return false;
+  }
+}
+
+template <typename T>
+bool launch_rows_os(bool forward, qtam_plan_s* pl, const void* in, void* out, int table, int64_t total_rows,
+                    hipStream_t st) {
+  using C = typename Complex<T>::type;
+  const HostPlan& hp = pl->hp;
+  switch (ilog2(pl->bs_len)) {
+#define X(LG)                                                                                          \
+  case LG:                                                                                             \
+    if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Os32 : kMaxLog2Os64)) {                            \
+      using Geo = RowGeom<T, (1 << LG)>;                                                               \
+      const int blocks = static_cast<int>((total_rows + Geo::G - 1) / Geo::G);                         \
+      if (forward)                                                                                     \
+        hipLaunchKernelGGL((k_fwd_rows_os<T, (1 << LG)>), dim3(unsigned(blocks)), dim3(Geo::NT), 0, st,  \
+                           static_cast<const C*>(in), static_cast<C*>(out), pl->d_rows,                \
+                           static_cast<const T*>(pl->d_tab[table]), hp.rows, int(total_rows),          \
+                           int(hp.half), pl->os, static_cast<const C*>(pl->d_bs_chirp),                \
+                           static_cast<const C*>(pl->d_bs_bf), static_cast<const C*>(pl->d_bs_tw), blocks); \
+      else                                                                                             \
+        hipLaunchKernelGGL((k_inv_rows_os<T, (1 << LG)>), dim3(unsigned(blocks)), dim3(Geo::NT), 0, st,  \
+                           static_cast<const C*>(in), static_cast<C*>(out), pl->d_rows,                \
+                           static_cast<const T*>(pl->d_tab[table]), hp.rows, int(total_rows),          \
+                           int(hp.sum_len), pl->os, static_cast<const C*>(pl->d_bs_chirp),             \
+                           static_cast<const C*>(pl->d_bs_bf), static_cast<const C*>(pl->d_bs_tw));    \
       return true;                                                                                     \
     }                                                                                                  \
     return false;
@@ -944,6 +1012,9 @@ bool analysis_rows(qtam_plan_s* pl, int table, void* y, int64_t segs, char* ws, 
     if (pl->bs_long) {
       Timed tm(pl, K_FWD_ROWS, st);
       if (!chirp_rows_long<T>(pl, true, table, spec, y, segs, ws, lay, st)) return false;
+    } else if (pl->bs_os) {
+      Timed tm(pl, K_FWD_ROWS, st);
+      if (!launch_rows_os<T>(true, pl, spec, y, table, segs * hp.rows, st)) return false;
     } else {
       Timed tm(pl, K_FWD_ROWS, st);
       if (!launch_rows_bs<T>(true, ilog2(pl->bs_len), spec, y, pl->d_rows, pl->d_tab[table], hp.rows, segs * hp.rows,
@@ -995,6 +1066,9 @@ bool inverse_rows(qtam_plan_s* pl, int table, const void* y, int64_t segs, char*
   } else if (pl->bluestein && pl->bs_long) {
     Timed tm(pl, K_INV_ROWS, st);
     ok = chirp_rows_long<T>(pl, false, table, y, pack, segs, ws, lay, st);
+  } else if (pl->bs_os) {
+    Timed tm(pl, K_INV_ROWS, st);
+    ok = launch_rows_os<T>(false, pl, y, pack, table, segs * hp.rows, st);
   } else if (pl->bluestein) {
     Timed tm(pl, K_INV_ROWS, st);
     ok = launch_rows_bs<T>(false, ilog2(pl->bs_len), y, pack, pl->d_rows, pl->d_tab[table], hp.rows, segs * hp.rows,
@@ -1256,6 +1330,58 @@ qtam_status run_op(qtam_plan_t pl, Op op, const void* in, void* out, int64_t bat
   return QTAM_OK;
 }
 
+// Overlap-save chirp-z rows (plain windows): the transform length L and the
+// blocks of every row. Transforms per row: one over the inputs and one per
+// block of outputs; the length that costs least by L log2 L is taken. Returns
+// false where no length has room for the widest support, or where other_cost
+// (the same measure of the forms that convolve a row at once) is less.
+constexpr int kOsMaxBlocks = 16;
+bool choose_overlap_save(qtam_plan_s* pl, double other_cost) {
+  const HostPlan& hp = pl->hp;
+  if (hp.eps > 0.0) return false;   // rows keep the whole band: slots modulo N_out
+  const int64_t M = hp.n_out;
+  int64_t jp = 0, jn = 0;
+  for (int k = 0; k < hp.rows; ++k) {
+    jp = std::max<int64_t>(jp, hp.hi[k] - hp.centre[k]);
+    jn = std::max<int64_t>(jn, hp.centre[k] - hp.lo[k]);
+  }
+  auto blocks_of = [&](int k, int64_t L, int64_t B) {   // block i covers the outputs below i B - JP + L + jlo
+    const int64_t left = M + jp - L + (hp.centre[k] - hp.lo[k]);
+    return left <= 0 ? int64_t(1) : 1 + (left + B - 1) / B;
+  };
+  double best = other_cost;
+  int64_t len = 0;
+  const int max_lg = hp.precision == QTAM_FP64 ? kMaxLog2Os64 : kMaxLog2Os32;
+  for (int lg = 2; lg <= max_lg; ++lg) {
+    const int64_t L = int64_t(1) << lg, B = L - jp - jn;
+    if (jp >= L / 2 || jn >= L / 2 || B < 1 || blocks_of(0, L, B) > kOsMaxBlocks) continue;
+    double cost = 0.0;
+    int64_t nmax = 1;
+    for (int k = 0; k < hp.rows; ++k) {
+      const int64_t nb = blocks_of(k, L, B);
+      nmax = std::max(nmax, nb);
+      cost += static_cast<double>(1 + nb) * static_cast<double>(L) * lg;
+    }
+    if (nmax > kOsMaxBlocks || cost >= best) continue;
+    best = cost;
+    len = L;
+    pl->os.B = static_cast<int>(B);
+    pl->os.nmax = static_cast<int>(nmax);
+  }
+  if (len == 0) return false;
+  pl->bs_len = len;
+  pl->os.M = static_cast<int>(M);
+  pl->os.JP = static_cast<int>(jp);
+  // a workgroup holds G consecutive rows and runs the most blocks any needs
+  const int64_t e = engine_e(len, hp.precision == QTAM_FP64), tpr = len / e, g = tpr >= 256 ? 1 : 256 / tpr;
+  pl->os_blocks.assign(hp.rows, 1);
+  for (int k = 0; k < hp.rows; ++k)
+    for (int64_t i = 0; i < std::min<int64_t>(g, hp.rows); ++i)
+      pl->os_blocks[k] = std::max<int>(pl->os_blocks[k],
+                                       static_cast<int>(blocks_of(static_cast<int>((k + i) % hp.rows), len, pl->os.B)));
+  return true;
+}
+
 // Which sizes the kernels cover; sets the four-step split of N/2.
 void choose_geometry(qtam_plan_s* pl) {
   const HostPlan& hp = pl->hp;
@@ -1273,7 +1399,13 @@ void choose_geometry(qtam_plan_s* pl) {
     pl->bs_len = lb;
     const int lg = ilog2(lb);
     if (lg < 2) return;
-    if (lg > max_single) {
+    // two transforms of length lb per row, one workgroup per CU at the longest;
+    // through the workspace they cost kLongChirp times that
+    constexpr double kAlone = 1.3, kLongChirp = 3.5;
+    const double other = 2.0 * static_cast<double>(lb) * lg * hp.rows *
+                         (lg > max_single ? kLongChirp : lg == max_single ? kAlone : 1.0);
+    pl->bs_os = choose_overlap_save(pl, other);
+    if (!pl->bs_os && lg > max_single) {
       pl->bs_long = true;
       const int l2 = lg / 2, l1 = lg - l2;   // bs_len = r1 * r2, r1 >= r2
       pl->r1 = int64_t(1) << l1;

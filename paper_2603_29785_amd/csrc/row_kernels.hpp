@@ -91,6 +91,10 @@ constexpr int kSStore = kCacheNT;
 // in a VGPR), so per-element offsets stay one add from a precomputed base
 // instead of being refolded into an add and a shift per resource.
 __device__ __forceinline__ void opaque(unsigned& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ int opaque_copy(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 
 // Row statistics (sum and max of |Y|^2 over the row) of the E values each of
 // a row's TPR threads holds. Lanes of one row inside a wave combine by an xor
@@ -507,6 +511,280 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows_bs(
     const C z = c_mul(v[i], c_conj(chirp[u]));
     const T w = tab[rm.off + d];
     srow[d] = C{z.x * w, z.y * w};
+  }
+}
+
+// Envelope lengths M = N_out that are not powers of two, plain windows: the
+// same identity by overlap-save. Row k has inputs only at the offsets j in
+// [jlo, jhi] = [lo - s, hi - s] of its support, so
+//   Y[m] = a[m] sum_j (g[j] a[j]) conj(a[m - j])
+// needs the chirp at lags m - j only. The outputs are taken in blocks: block i
+// holds the lags V_i .. V_i + L - 1, V_i = -JP + i B (JP, JN the largest
+// positive and negative offsets of any row, B = L - JP - JN), and one cyclic
+// convolution of length L with them gives every m with V_i + jhi <= m <
+// V_i + L + jlo, which is block i of this row up to where block i + 1 starts.
+// The transform of the inputs is shared by a row's blocks: 1 + blocks
+// transforms of length L per row, where one convolution over all outputs
+// takes two of length >= 2 M - 1. A row of narrow support needs fewer blocks.
+// The inverse is its transpose: the blocks' transforms times conj(Bhat_i) add
+// up in registers, then one inverse transform. Bhat_i = FFT_L(conj a[V_i + t])
+// / L, t = 0 .. L - 1 (built in FP64).
+// The output registers of a transform hold the same indices as the input
+// registers of the next one in another order (both sets are the multiples of
+// TPR), so no exchange stands between the two.
+// What bounds it: vector ALU issue and the latency between its transforms
+// (registers and LDS, packed FP32 off), as in the other row kernels; four
+// waves per SIMD, so the table loads of a block's transforms are kept from
+// being hoisted out of the block loop (they would take 64 registers and spill).
+// Measured on MI355X, FP32, 62 rows of 24576-sample segments: forward + inverse
+// of 128 segments with N_out = 12289 (support 1537) 11.45 ms by length-32768
+// transforms through memory, 0.88 ms here (L = 4096, 4 or 5 blocks); forward of
+// 1024 segments with N_out = 1028 (support 1027) 0.87 ms by one length-4096
+// convolution per row, 0.72 ms here (L = 2048, one block for rows of at most
+// 507 bins a side, else two).
+struct OsPlan {
+  int M, JP, B;          // N_out, largest positive offset, block step
+  int nmax;              // blocks of the table Bhat
+  const int* blocks;     // [R] blocks needed by the rows of a workgroup that starts at this row
+};
+
+// Input register of F2 that holds the index of output register i of F1.
+template <typename F1, typename F2, int E>
+constexpr int os_in_reg(int i) {
+  for (int k = 0; k < E; ++k)
+    if (F2::in_off(k) == F1::out_off(i)) return k;
+  return -1;
+}
+
+template <typename T, int L>
+__global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
+    const typename Complex<T>::type* __restrict__ spec, typename Complex<T>::type* __restrict__ Y,
+    const RowMeta* __restrict__ rows, const T* __restrict__ tab, int R, int total, int half, OsPlan os,
+    const typename Complex<T>::type* __restrict__ chirp, const typename Complex<T>::type* __restrict__ bhat,
+    const typename Complex<T>::type* __restrict__ tw, int nblocks) {
+  using C = typename Complex<T>::type;
+  using Geo = RowGeom<T, L>;
+  using F = BlockFft<T, L, Geo::E, -1, TW_MIXED>;
+  using Fi = BlockFft<T, L, Geo::E, +1, TW_MIXED>;
+  constexpr bool kWaveRow = Geo::TPR >= 64;
+  __shared__ C lds[Geo::G * lds_size(L)];
+  const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
+  C* reg = lds + g * lds_size(L);
+  const int u = xcd_major_block(nblocks);
+  int gr = u * Geo::G + g;
+  if constexpr (kWaveRow) gr = __builtin_amdgcn_readfirstlane(gr);
+  const bool ok = gr < total;
+  const int seg = ok ? gr / R : 0;
+  const RowMeta rm = rows[ok ? gr - seg * R : 0];
+  const int len = ok ? rm.hi - rm.lo + 1 : 0;
+  const int jlo = rm.lo - rm.s, jhi = rm.hi - rm.s;
+  const int nb = __builtin_amdgcn_readfirstlane(os.blocks[(u * Geo::G) % R]);
+  const rsrc_t rc = make_rsrc(chirp, static_cast<uint32_t>(os.M * sizeof(C)));
+  C v[Geo::E];
+  {
+    // kept bins c = s + j at slot j mod L (j the signed slot), times the table
+    // and the chirp; slots outside the support read 0
+    const C* Z = spec + int64_t(seg) * half;
+    const C z0 = Z[0];   // (X[0], X[N/2])
+    const int db = tl - jlo;   // d = c - lo of the slot with offset 0
+    rsrc_t rz, rt;
+    if constexpr (kWaveRow) {
+      rz = make_rsrc(Z + rm.lo, static_cast<uint32_t>((ok && rm.hi == half ? len - 1 : len) * sizeof(C)));
+      rt = make_rsrc(tab + rm.off, static_cast<uint32_t>(len * sizeof(T)));
+    }
+    unsigned bx = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(C));
+    unsigned bw = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(T));
+    unsigned bp = static_cast<unsigned>(tl) * static_cast<unsigned>(sizeof(C)), bn = 0u - bp;   // chirp[|j|]
+    opaque(bx);
+    opaque(bw);
+    opaque(bp);
+    opaque(bn);
+#pragma unroll
+    for (int i = 0; i < Geo::E; ++i) {
+      const int off = F::in_off(i);
+      const bool pos = off < L / 2;
+      const unsigned j = static_cast<unsigned>(pos ? off : off - L);
+      C x{0, 0};
+      T w = 0;
+      if constexpr (kWaveRow) {
+        x = bload<C>(rz, bx + j * static_cast<unsigned>(sizeof(C)));
+        w = bload<T>(rt, bw + j * static_cast<unsigned>(sizeof(T)));
+      } else {
+        const int d = db + static_cast<int>(j);
+        if (static_cast<unsigned>(d) < static_cast<unsigned>(len)) {
+          x = Z[rm.lo + d == half ? 0 : rm.lo + d];
+          w = tab[rm.off + d];
+        }
+      }
+      const C a = bload<C>(rc, pos ? bp + static_cast<unsigned>(off * int(sizeof(C)))
+                                   : bn + static_cast<unsigned>((L - off) * int(sizeof(C))));
+      v[i] = c_mul(C{x.x * w, x.y * w}, a);
+    }
+    if (rm.lo == 0 || rm.hi == half) {
+#pragma unroll
+      for (int i = 0; i < Geo::E; ++i) {
+        const int off = F::in_off(i);
+        const int c = rm.s + tl + (off < L / 2 ? off : off - L);
+        const bool dc = c == 0 && rm.lo == 0, ny = c == half && rm.hi == half;
+        if (ok && (dc || ny)) {
+          const T w = (dc ? z0.x : z0.y) * tab[rm.off + (c - rm.lo)];
+          const C a = chirp[c < rm.s ? rm.s - c : c - rm.s];
+          v[i] = C{w * a.x, w * a.y};
+        }
+      }
+    }
+  }
+  int nz = 0;
+  if constexpr (kWaveRow && F::R0 == 16 && Geo::E == 16) {
+    const int t0 = __builtin_amdgcn_readfirstlane(tl) & ~63;
+    constexpr int Q = L / 16;   // input i of lane tl sits at slot tl + i Q
+    auto zero = [&](int a, int b) { return t0 + a * Q > jhi && t0 + 63 + b * Q < L + jlo; };
+    nz = zero(1, 14) ? 2 : (zero(2, 13) ? 4 : 0);
+  }
+  F::run(v, reg, tl, F::twiddles(tw), nz);
+  C* yrow = Y + int64_t(ok ? gr : 0) * os.M;
+  const rsrc_t rb = make_rsrc(bhat, static_cast<uint32_t>(os.nmax * L * int(sizeof(C))));
+  int done = 0;   // outputs already stored
+  for (int b = 0; b < nb; ++b) {
+    const int tb = opaque_copy(tl);   // keeps the transform's table loads in the loop (registers)
+    C z[Geo::E];
+#pragma unroll
+    for (int i = 0; i < Geo::E; ++i) {
+      constexpr auto in_reg = os_in_reg<F, Fi, Geo::E>;
+      z[in_reg(i)] = c_mul(v[i], bload<C>(rb, static_cast<uint32_t>(tl) * sizeof(C),
+                                          static_cast<uint32_t>(b * L + F::out_off(i)) * sizeof(C)));
+    }
+    Fi::run(z, reg, tb, Fi::twiddles(tw));
+    const int V = b * os.B - os.JP;
+    const int end = V + L + jlo < os.M ? V + L + jlo : os.M;
+    if (ok && end > done) {
+      // outputs done .. end - 1, at t = m - V
+      unsigned bc = static_cast<unsigned>(V + tl) * static_cast<unsigned>(sizeof(C));
+      unsigned bs = static_cast<unsigned>(V + tl - done) * static_cast<unsigned>(sizeof(C));
+      opaque(bc);
+      opaque(bs);
+      rsrc_t ry;
+      if constexpr (kWaveRow) ry = make_rsrc(yrow + done, static_cast<uint32_t>((end - done) * sizeof(C)));
+#pragma unroll
+      for (int i = 0; i < Geo::E; ++i) {
+        const unsigned o = static_cast<unsigned>(Fi::out_off(i)) * static_cast<unsigned>(sizeof(C));
+        const C y = c_mul(z[i], bload<C>(rc, bc + o));
+        if constexpr (kWaveRow) {
+          bstore<C, kYStore>(ry, y, bs + o);
+        } else {
+          const int m = V + tl + Fi::out_off(i);
+          if (m >= done && m < end) yrow[m] = y;
+        }
+      }
+      done = end;
+    }
+  }
+}
+
+template <typename T, int L>
+__global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_inv_rows_os(
+    const typename Complex<T>::type* __restrict__ Y, typename Complex<T>::type* __restrict__ Sbuf,
+    const RowMeta* __restrict__ rows, const T* __restrict__ tab, int R, int total, int sum_len, OsPlan os,
+    const typename Complex<T>::type* __restrict__ chirp, const typename Complex<T>::type* __restrict__ bhat,
+    const typename Complex<T>::type* __restrict__ tw) {
+  using C = typename Complex<T>::type;
+  using Geo = RowGeom<T, L>;
+  using F = BlockFft<T, L, Geo::E, -1, TW_MIXED>;
+  using Fi = BlockFft<T, L, Geo::E, +1, TW_MIXED>;
+  constexpr bool kWaveRow = Geo::TPR >= 64;
+  __shared__ C lds[Geo::G * lds_size(L)];
+  const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
+  C* reg = lds + g * lds_size(L);
+  const int u = static_cast<int>(blockIdx.x);
+  int gr = u * Geo::G + g;
+  if constexpr (kWaveRow) gr = __builtin_amdgcn_readfirstlane(gr);
+  const bool ok = gr < total;
+  const int seg = ok ? gr / R : 0;
+  const RowMeta rm = rows[ok ? gr - seg * R : 0];
+  const int len = ok ? rm.hi - rm.lo + 1 : 0;
+  const int jlo = rm.lo - rm.s;
+  const int nb = __builtin_amdgcn_readfirstlane(os.blocks[(u * Geo::G) % R]);
+  const rsrc_t rc = make_rsrc(chirp, static_cast<uint32_t>(os.M * sizeof(C)));
+  const rsrc_t rb = make_rsrc(bhat, static_cast<uint32_t>(os.nmax * L * int(sizeof(C))));
+  const C* yrow = Y + int64_t(ok ? gr : 0) * os.M;
+  C acc[Geo::E];
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) acc[i] = C{0, 0};
+  int done = 0;
+  for (int b = 0; b < nb; ++b) {
+    const int V = b * os.B - os.JP;
+    int end = V + L + jlo < os.M ? V + L + jlo : os.M;
+    if (!ok || end < done) end = done;
+    unsigned bc = static_cast<unsigned>(V + tl) * static_cast<unsigned>(sizeof(C));
+    unsigned by = static_cast<unsigned>(V + tl - done) * static_cast<unsigned>(sizeof(C));
+    opaque(bc);
+    opaque(by);
+    rsrc_t ry;
+    if constexpr (kWaveRow) ry = make_rsrc(yrow + done, static_cast<uint32_t>((end - done) * sizeof(C)));
+    C v[Geo::E];
+#pragma unroll
+    for (int i = 0; i < Geo::E; ++i) {
+      const unsigned o = static_cast<unsigned>(F::in_off(i)) * static_cast<unsigned>(sizeof(C));
+      C y{0, 0};
+      if constexpr (kWaveRow) {
+        y = bload<C>(ry, by + o);
+      } else {
+        const int m = V + tl + F::in_off(i);
+        if (m >= done && m < end) y = yrow[m];
+      }
+      v[i] = c_mul(y, c_conj(bload<C>(rc, bc + o)));
+    }
+    F::run(v, reg, opaque_copy(tl), F::twiddles(tw));   // (table loads stay in the loop: registers)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < Geo::E; ++i) {
+      const C h = c_conj(bload<C>(rb, static_cast<uint32_t>(tl) * sizeof(C),
+                                  static_cast<uint32_t>(b * L + F::out_off(i)) * sizeof(C)));
+      acc[i] = C{fmadd(v[i].x, h.x, fmadd(-v[i].y, h.y, acc[i].x)), fmadd(v[i].x, h.y, fmadd(v[i].y, h.x, acc[i].y))};
+    }
+    done = end;
+  }
+  C z[Geo::E];
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) {
+    constexpr auto in_reg = os_in_reg<F, Fi, Geo::E>;
+    z[in_reg(i)] = acc[i];
+  }
+  Fi::run(z, reg, tl, Fi::twiddles(tw));
+  if (!ok) return;
+  // slot j mod L holds the kept entry d = j - jlo
+  const int db = tl - jlo;
+  C* srow = Sbuf + int64_t(seg) * sum_len + rm.off;
+  rsrc_t rs, rt;
+  if constexpr (kWaveRow) {
+    rs = make_rsrc(srow, static_cast<uint32_t>(len * sizeof(C)));
+    rt = make_rsrc(tab + rm.off, static_cast<uint32_t>(len * sizeof(T)));
+  }
+  unsigned bs = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(C));
+  unsigned bw = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(T));
+  unsigned bp = static_cast<unsigned>(tl) * static_cast<unsigned>(sizeof(C)), bn = 0u - bp;
+  opaque(bs);
+  opaque(bw);
+  opaque(bp);
+  opaque(bn);
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) {
+    const int off = Fi::out_off(i);
+    const bool pos = off < L / 2;
+    const unsigned j = static_cast<unsigned>(pos ? off : off - L);
+    const C a = bload<C>(rc, pos ? bp + static_cast<unsigned>(off * int(sizeof(C)))
+                                 : bn + static_cast<unsigned>((L - off) * int(sizeof(C))));
+    const C x = c_mul(z[i], c_conj(a));
+    if constexpr (kWaveRow) {
+      const T w = bload<T>(rt, bw + j * static_cast<unsigned>(sizeof(T)));
+      bstore<C, kSStore>(rs, C{x.x * w, x.y * w}, bs + j * static_cast<unsigned>(sizeof(C)));
+    } else {
+      const int d = db + static_cast<int>(j);
+      if (static_cast<unsigned>(d) < static_cast<unsigned>(len)) {
+        const T w = tab[rm.off + d];
+        srow[d] = C{x.x * w, x.y * w};
+      }
+    }
   }
 }
 
