@@ -66,6 +66,7 @@ enum Table { T_FWD = 0, T_DUAL = 1, T_AFWD = 2, T_AINV = 3, T_DENSE = 4, T_TILE 
 
 constexpr int kMaxLog2Single32 = 14;   // LDS-resident FFT up to 16384 points (FP32)
 constexpr int kMaxLog2Single64 = 13;   // and 8192 points (FP64)
+constexpr int kMaxLog2Seg = 13;        // spectra and synthesis transforms in one pass: M2 up to 8192
 // Envelope rows in one workgroup: up to 32768 points in FP32 (1024 threads x
 // 32 values, exchanges through LDS in two halves), 8192 in FP64.
 constexpr int kMaxLog2Rows32 = 15;
@@ -510,7 +511,8 @@ struct Timed {
 #define QTAM_POW2_CASES(X) \
   X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
 
-template <typename T, int S>
+// RIN, ROUT: decimated input / interleaved output (one transform per workgroup).
+template <typename T, int S, int RIN = 1, int ROUT = 1>
 bool launch_fft_rows(int log2l, const void* in, void* out, int64_t count, int64_t stride, const void* tw,
                      hipStream_t st) {
   using C = typename Complex<T>::type;
@@ -519,11 +521,13 @@ bool launch_fft_rows(int log2l, const void* in, void* out, int64_t count, int64_
   case LG:                                                                                         \
     if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Single32 : kMaxLog2Single64)) {               \
       using Geo = RowGeom<T, (1 << LG)>;                                                           \
-      const int64_t blocks = (count + Geo::G - 1) / Geo::G;                                        \
-      hipLaunchKernelGGL((k_fft_rows<T, (1 << LG), S>), dim3(unsigned(blocks)), dim3(Geo::NT), 0, st, \
-                         static_cast<const C*>(in), static_cast<C*>(out), count, stride,            \
-                         static_cast<const C*>(tw));                                               \
-      return true;                                                                                 \
+      if constexpr ((RIN == 1 && ROUT == 1) || Geo::G == 1) {                                      \
+        const int64_t blocks = (count + Geo::G - 1) / Geo::G;                                      \
+        hipLaunchKernelGGL((k_fft_rows<T, (1 << LG), S, RIN, ROUT>), dim3(unsigned(blocks)),       \
+                           dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out),  \
+                           count, stride, static_cast<const C*>(tw));                              \
+        return true;                                                                               \
+      }                                                                                            \
     }                                                                                              \
     return false;
     QTAM_POW2_CASES(X)
@@ -536,7 +540,7 @@ bool launch_fft_rows(int log2l, const void* in, void* out, int64_t count, int64_
 constexpr int kMaxLog2Col32 = 12;   // four-step sub-FFTs up to 4096 points (FP32)
 constexpr int kMaxLog2Col64 = 11;   // and 2048 points (FP64)
 
-template <typename T, int S>
+template <typename T, int S, int RIN = 1>
 bool launch_fft_cols(int log2l, const void* in, void* out, int64_t n1, int64_t segs, int64_t seg_stride,
                      const void* tw, Twiddle2<typename Complex<T>::type> tw2, hipStream_t st, int tw_mul = 2) {
   using C = typename Complex<T>::type;
@@ -546,14 +550,14 @@ bool launch_fft_cols(int log2l, const void* in, void* out, int64_t n1, int64_t s
     if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Col32 : kMaxLog2Col64)) {                     \
       using GeoW = ColGeom<T, (1 << LG), 0, kColWide>;                                            \
       if (n1 % GeoW::CC == 0) {                                                                   \
-        hipLaunchKernelGGL((k_fft_cols<T, (1 << LG), S, kColWide>), dim3(unsigned(n1 / GeoW::CC), unsigned(segs)), \
+        hipLaunchKernelGGL((k_fft_cols<T, (1 << LG), S, kColWide, RIN>), dim3(unsigned(n1 / GeoW::CC), unsigned(segs)), \
                            dim3(GeoW::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n1, \
                            seg_stride, static_cast<const C*>(tw), tw2, tw_mul);                   \
         return true;                                                                              \
       }                                                                                           \
       using Geo = ColGeom<T, (1 << LG)>;                                                          \
       if (n1 % Geo::CC) return false;                                                             \
-      hipLaunchKernelGGL((k_fft_cols<T, (1 << LG), S>), dim3(unsigned(n1 / Geo::CC), unsigned(segs)), \
+      hipLaunchKernelGGL((k_fft_cols<T, (1 << LG), S, 0, RIN>), dim3(unsigned(n1 / Geo::CC), unsigned(segs)), \
                          dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n1, \
                          seg_stride, static_cast<const C*>(tw), tw2, tw_mul);                     \
       return true;                                                                                \
@@ -565,7 +569,7 @@ bool launch_fft_cols(int log2l, const void* in, void* out, int64_t n1, int64_t s
   }
 }
 
-template <typename T, int S, int EP = 0>
+template <typename T, int S, int EP = 0, int ROUT = 1>
 bool launch_fft_rows_t(int log2l, const void* in, void* out, int64_t n2, int64_t segs, int64_t seg_stride,
                        const void* tw, hipStream_t st) {
   using C = typename Complex<T>::type;
@@ -576,20 +580,49 @@ bool launch_fft_rows_t(int log2l, const void* in, void* out, int64_t n2, int64_t
       constexpr int CW = EP == 0 ? kRowWide : 0;                                                    \
       using GeoW = ColGeom<T, (1 << LG), EP, CW>;                                                   \
       if (n2 % GeoW::CC == 0) {                                                                     \
-        hipLaunchKernelGGL((k_fft_rows_t<T, (1 << LG), S, EP, CW>), dim3(unsigned(n2 / GeoW::CC), unsigned(segs)), \
+        hipLaunchKernelGGL((k_fft_rows_t<T, (1 << LG), S, EP, CW, ROUT>), dim3(unsigned(n2 / GeoW::CC), unsigned(segs)), \
                            dim3(GeoW::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2, \
                            seg_stride, static_cast<const C*>(tw));                                  \
         return true;                                                                                \
       }                                                                                             \
       using Geo = ColGeom<T, (1 << LG), EP>;                                                        \
       if (n2 % Geo::CC) return false;                                                               \
-      hipLaunchKernelGGL((k_fft_rows_t<T, (1 << LG), S, EP>), dim3(unsigned(n2 / Geo::CC), unsigned(segs)), \
+      hipLaunchKernelGGL((k_fft_rows_t<T, (1 << LG), S, EP, 0, ROUT>), dim3(unsigned(n2 / Geo::CC), unsigned(segs)), \
                          dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2,  \
                          seg_stride, static_cast<const C*>(tw));                                    \
       return true;                                                                                  \
     }                                                                                               \
     return false;
     QTAM_COL_CASES(X)
+#undef X
+    default: return false;
+  }
+}
+
+// Whole spectrum (S = -1) or synthesis transform (S = +1) of segments that fit
+// one workgroup (one_workgroup).
+template <typename T, int S, int R>
+bool launch_seg(int log2m2, const void* in, void* out, int64_t segs, const void* tw,
+                Twiddle2<typename Complex<T>::type> tw2, hipStream_t st) {
+  using C = typename Complex<T>::type;
+  switch (log2m2) {
+#define X(LG)                                                                                       \
+  case LG:                                                                                          \
+    if constexpr ((LG) >= 3 && (LG) <= kMaxLog2Seg) {                                               \
+      using Geo = SegGeom<T, (1 << LG), R>;                                                         \
+      if constexpr (Geo::FITS) {                                                                    \
+        const dim3 grid(unsigned((segs + Geo::G - 1) / Geo::G));                                    \
+        if constexpr (S < 0)                                                                        \
+          hipLaunchKernelGGL((k_spec_seg<T, (1 << LG), R>), grid, dim3(Geo::NT), 0, st,             \
+                             static_cast<const C*>(in), static_cast<C*>(out), segs, static_cast<const C*>(tw), tw2); \
+        else                                                                                        \
+          hipLaunchKernelGGL((k_syn_seg<T, (1 << LG), R>), grid, dim3(Geo::NT), 0, st,              \
+                             static_cast<const C*>(in), static_cast<C*>(out), segs, static_cast<const C*>(tw), tw2); \
+        return true;                                                                                \
+      }                                                                                             \
+    }                                                                                               \
+    return false;
+    QTAM_POW2_CASES(X)
 #undef X
     default: return false;
   }
@@ -848,41 +881,70 @@ Twiddle2<typename Complex<T>::type> tw2_of(const qtam_plan_s* pl) {
 
 // count length-M2 transforms (sign S) of consecutive M2-element blocks: one
 // LDS pass, or two passes through `tmp` (then `tmp` must differ from both).
-template <typename T, int S>
+// RIN, ROUT = r: of the decimated signal, into the interleaved signal.
+template <typename T, int S, int RIN = 1, int ROUT = 1>
 bool transform_m2(qtam_plan_s* pl, const void* in, void* out, void* tmp, int64_t count, hipStream_t st, int k_one,
                   int k_pass1, int k_pass2) {
   const int64_t m2 = pl->m2;
   if (!pl->four_step) {
     Timed tm(pl, k_one, st);
-    return launch_fft_rows<T, S>(ilog2(m2), in, out, count, m2, pl->d_tw_half, st);
+    return launch_fft_rows<T, S, RIN, ROUT>(ilog2(m2), in, out, count, m2, pl->d_tw_half, st);
   }
   bool ok;
   {
     Timed tm(pl, k_pass1, st);
-    ok = launch_fft_cols<T, S>(ilog2(pl->n2), in, tmp, pl->n1, count, m2, pl->d_tw_n2, tw2_of<T>(pl), st,
-                               static_cast<int>(2 * pl->radix_r));
+    ok = launch_fft_cols<T, S, RIN>(ilog2(pl->n2), in, tmp, pl->n1, count, m2, pl->d_tw_n2, tw2_of<T>(pl), st,
+                                    static_cast<int>(2 * pl->radix_r));
   }
   if (!ok) return false;
   Timed tm(pl, k_pass2, st);
-  return launch_fft_rows_t<T, S, kPass2E>(ilog2(pl->n1), tmp, out, pl->n2, count, m2, pl->d_tw_n1, st);
+  return launch_fft_rows_t<T, S, kPass2E, ROUT>(ilog2(pl->n1), tmp, out, pl->n2, count, m2, pl->d_tw_n1, st);
 }
 
-// Radix-r combination of the decimated transforms (S = -1, analysis) or its
-// inverse (S = +1, synthesis), over segs segments.
-template <typename T, int S>
-bool launch_radix(qtam_plan_s* pl, const void* in, void* out, int64_t segs, hipStream_t st) {
+// Whether a segment's N/2 = R * M2 values fit one workgroup (as SegGeom: LDS
+// for R padded regions, at most 1024 threads).
+template <typename T, int R>
+bool one_workgroup(const qtam_plan_s* pl) {
+  const int64_t tpr = pl->m2 / engine_e(pl->m2, sizeof(T) == 8);
+  return !pl->four_step && R * tpr <= 1024 &&
+         (R * tpr < 256 || size_t(R) * size_t(lds_size(static_cast<int>(pl->m2))) * 2 * sizeof(T) <= 160u * 1024u);
+}
+
+// Spectrum of segments with N/2 = R * M2: in one workgroup, or the decimated
+// transforms (x -> rows `f`) and the combination with the twist.
+template <typename T, int R>
+bool spectrum_r(qtam_plan_s* pl, const void* x, void* spec, void* f, void* tmp, int64_t segs, hipStream_t st) {
   using C = typename Complex<T>::type;
-  Timed tm(pl, S < 0 ? K_SPEC_RADIX : K_SYN_RADIX, st);
-  const dim3 grid(unsigned((pl->m2 + 255) / 256), unsigned(segs));
-  if (pl->radix_r == 3)
-    hipLaunchKernelGGL((k_radix<T, 3, S>), grid, dim3(256), 0, st, static_cast<const C*>(in), static_cast<C*>(out),
-                       pl->m2, tw2_of<T>(pl));
-  else if (pl->radix_r == 5)
-    hipLaunchKernelGGL((k_radix<T, 5, S>), grid, dim3(256), 0, st, static_cast<const C*>(in), static_cast<C*>(out),
-                       pl->m2, tw2_of<T>(pl));
-  else
-    return false;
-  return true;
+  if (one_workgroup<T, R>(pl)) {
+    Timed tm(pl, K_SPEC, st);
+    return launch_seg<T, -1, R>(ilog2(pl->m2), x, spec, segs, pl->d_tw_half, tw2_of<T>(pl), st);
+  }
+  if constexpr (R > 1) {
+    if (!transform_m2<T, -1, R>(pl, x, f, tmp, segs * R, st, K_SPEC, K_SPEC1, K_SPEC2)) return false;
+    Timed tm(pl, K_SPEC_RADIX, st);
+    hipLaunchKernelGGL((k_radix_twist<T, R>), dim3(unsigned((pl->m2 / 2 + 256) / 256), unsigned(segs)), dim3(256), 0, st,
+                       static_cast<const C*>(f), static_cast<C*>(spec), pl->m2, tw2_of<T>(pl));
+    return true;
+  }
+  return false;
+}
+
+// Synthesis transform of segments with N/2 = R * M2 (R = 3, 5): in one
+// workgroup, or the radix-R split into rows `a`, their transforms and the
+// interleaved store.
+template <typename T, int R>
+bool synthesis_r(qtam_plan_s* pl, const void* spec, void* x, void* a, void* tmp, int64_t segs, hipStream_t st) {
+  using C = typename Complex<T>::type;
+  if (one_workgroup<T, R>(pl)) {
+    Timed tm(pl, K_SYN, st);
+    return launch_seg<T, +1, R>(ilog2(pl->m2), spec, x, segs, pl->d_tw_half, tw2_of<T>(pl), st);
+  }
+  {
+    Timed tm(pl, K_SYN_RADIX, st);
+    hipLaunchKernelGGL((k_radix<T, R>), dim3(unsigned((pl->m2 + 255) / 256), unsigned(segs)), dim3(256), 0, st,
+                       static_cast<const C*>(spec), static_cast<C*>(a), pl->m2, tw2_of<T>(pl));
+  }
+  return transform_m2<T, +1, 1, R>(pl, a, x, tmp, segs * R, st, K_SYN, K_SYN1, K_SYN2);
 }
 
 // analysis, first half: real signal x -> its spectrum in ws + lay.spec (bins
@@ -894,44 +956,19 @@ bool analysis_spectrum(qtam_plan_s* pl, const void* x, int64_t segs, char* ws, c
   const HostPlan& hp = pl->hp;
   const int64_t half = hp.half;
   void* spec = ws + lay.spec;
-  bool ok;
-  bool twisted = false;
-  if (pl->radix_r == 1 && pl->four_step) {
-    // first pass, then the second pass with the real-signal twist folded in
-    void* tmp = ws + lay.tmp;
-    {
-      Timed tm(pl, K_SPEC1, st);
-      ok = launch_fft_cols<T, -1>(ilog2(pl->n2), x, tmp, pl->n1, segs, half, pl->d_tw_n2, tw2_of<T>(pl), st, 2);
-    }
-    if (ok) {
-      Timed tm(pl, K_SPEC2, st);
-      ok = launch_spec_rows_twist<T>(ilog2(pl->n1), tmp, spec, pl->n2, segs, half, pl->d_tw_n1, tw2_of<T>(pl), st);
-    }
-    twisted = true;
-  } else if (pl->radix_r == 1) {
-    ok = transform_m2<T, -1>(pl, x, spec, ws + lay.tmp, segs, st, K_SPEC, K_SPEC1, K_SPEC2);
-  } else {
-    using C = typename Complex<T>::type;
-    void* tmp = ws + lay.tmp;
-    void* tmp2 = ws + lay.tmp2;
-    {
-      Timed tm(pl, K_SPEC_PERM, st);
-      hipLaunchKernelGGL((k_permute<T, true>), dim3(unsigned((half + 255) / 256), unsigned(segs)), dim3(256), 0, st,
-                         static_cast<const C*>(x), static_cast<C*>(tmp2), pl->radix_r, pl->m2);
-    }
-    // single pass: tmp2 -> tmp; four-step: tmp2 -> tmp -> tmp2
-    void* f = pl->four_step ? tmp2 : tmp;
-    ok = transform_m2<T, -1>(pl, tmp2, f, tmp, segs * pl->radix_r, st, K_SPEC, K_SPEC1, K_SPEC2);
-    if (ok) ok = launch_radix<T, -1>(pl, f, spec, segs, st);
+  void* tmp = ws + lay.tmp;
+  void* tmp2 = ws + lay.tmp2;
+  if (pl->radix_r == 3) return spectrum_r<T, 3>(pl, x, spec, tmp2, tmp, segs, st);
+  if (pl->radix_r == 5) return spectrum_r<T, 5>(pl, x, spec, tmp2, tmp, segs, st);
+  if (!pl->four_step) return spectrum_r<T, 1>(pl, x, spec, nullptr, nullptr, segs, st);
+  // first pass, then the second pass with the real-signal twist folded in
+  {
+    Timed tm(pl, K_SPEC1, st);
+    if (!launch_fft_cols<T, -1>(ilog2(pl->n2), x, tmp, pl->n1, segs, half, pl->d_tw_n2, tw2_of<T>(pl), st, 2))
+      return false;
   }
-  if (!ok) return false;
-  if (!twisted) {
-    using C = typename Complex<T>::type;
-    Timed tm(pl, K_TWIST, st);
-    hipLaunchKernelGGL((k_twist<T>), dim3(unsigned((half / 2 + 1 + 255) / 256), unsigned(segs)), dim3(256), 0, st,
-                       static_cast<C*>(spec), half, tw2_of<T>(pl));
-  }
-  return true;
+  Timed tm(pl, K_SPEC2, st);
+  return launch_spec_rows_twist<T>(ilog2(pl->n1), tmp, spec, pl->n2, segs, half, pl->d_tw_n1, tw2_of<T>(pl), st);
 }
 
 // Chirp-z rows beyond one workgroup, for one chunk: the length-L cyclic
@@ -1111,15 +1148,8 @@ bool synthesize(qtam_plan_s* pl, const void* pack, int64_t slen, const int* star
                        tw2_of<T>(pl));
   }
   if (pl->radix_r == 1) return transform_m2<T, +1>(pl, spec, x, ws + lay.tmp, segs, st, K_SYN, K_SYN1, K_SYN2);
-  void* tmp = ws + lay.tmp;
-  void* tmp2 = ws + lay.tmp2;
-  if (!launch_radix<T, +1>(pl, spec, tmp2, segs, st)) return false;
-  void* f = pl->four_step ? tmp2 : tmp;
-  if (!transform_m2<T, +1>(pl, tmp2, f, tmp, segs * pl->radix_r, st, K_SYN, K_SYN1, K_SYN2)) return false;
-  Timed tm(pl, K_SYN_PERM, st);
-  hipLaunchKernelGGL((k_permute<T, false>), dim3(unsigned((half + 255) / 256), unsigned(segs)), dim3(256), 0, st,
-                     static_cast<const C*>(f), static_cast<C*>(x), pl->radix_r, pl->m2);
-  return true;
+  return pl->radix_r == 3 ? synthesis_r<T, 3>(pl, spec, x, ws + lay.tmp2, ws + lay.tmp, segs, st)
+                          : synthesis_r<T, 5>(pl, spec, x, ws + lay.tmp2, ws + lay.tmp, segs, st);
 }
 
 // Dense tiles of a chunk: the kept DFT_{N_out} slots of every row (scaled),
@@ -1154,10 +1184,10 @@ bool run_dense(qtam_plan_s* pl, const void* y, void* dense, int64_t segs, char* 
     Timed tm(pl, K_DENSE_RADIX, st);
     const dim3 grid(unsigned((md + 255) / 256), unsigned(count));
     if (r == 3)
-      hipLaunchKernelGGL((k_radix<T, 3, +1, 1>), grid, dim3(256), 0, st, static_cast<const C*>(a),
+      hipLaunchKernelGGL((k_radix<T, 3, 1>), grid, dim3(256), 0, st, static_cast<const C*>(a),
                          static_cast<C*>(b), md, tw2_of<T>(pl));
     else if (r == 5)
-      hipLaunchKernelGGL((k_radix<T, 5, +1, 1>), grid, dim3(256), 0, st, static_cast<const C*>(a),
+      hipLaunchKernelGGL((k_radix<T, 5, 1>), grid, dim3(256), 0, st, static_cast<const C*>(a),
                          static_cast<C*>(b), md, tw2_of<T>(pl));
     else
       return false;
@@ -1182,7 +1212,7 @@ bool run_dense(qtam_plan_s* pl, const void* y, void* dense, int64_t segs, char* 
   }
   if (!ok || r == 1) return ok;
   Timed tm(pl, K_DENSE_PERM, st);
-  hipLaunchKernelGGL((k_permute<T, false>), dim3(unsigned((hp.n + 255) / 256), unsigned(count)), dim3(256), 0, st,
+  hipLaunchKernelGGL((k_permute<T>), dim3(unsigned((hp.n + 255) / 256), unsigned(count)), dim3(256), 0, st,
                      static_cast<const C*>(b), static_cast<C*>(a), r, md);
   return true;
 }
@@ -1436,7 +1466,7 @@ void choose_geometry(qtam_plan_s* pl) {
   }
   const int lh = ilog2(pl->m2);
   if (lh < 3) return;
-  if (lh <= std::min(max_single, 13)) {
+  if (lh <= kMaxLog2Seg) {
     pl->four_step = false;
   } else {
     pl->four_step = true;
