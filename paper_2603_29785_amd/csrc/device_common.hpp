@@ -80,4 +80,16 @@ struct ColGeom {
   static constexpr int NT = CC * TPR;
 };
 
+// Workgroups go round-robin over the 8 XCDs, each with its own L2. Where R
+// sibling workgroups share cache lines (decimated reads, interleaved writes),
+// workgroup b of units * R takes sibling s of unit v such that the siblings
+// of a unit are a multiple of 8 apart: one XCD, at nearly the same time, so
+// its L2 joins their parts of a line.
+template <int R>
+__device__ __forceinline__ void sibling_block(int64_t b, int64_t units, int64_t& v, int& s) {
+  const int64_t v0 = b / (8 * R) * 8, m = units - v0 < 8 ? units - v0 : 8, k = b - v0 * R;
+  v = v0 + k % m;
+  s = static_cast<int>(k / m);
+}
+
 }  // namespace qtam

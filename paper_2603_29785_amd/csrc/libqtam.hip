@@ -1153,68 +1153,66 @@ bool synthesize(qtam_plan_s* pl, const void* pack, int64_t slen, const int* star
 }
 
 // Dense tiles of a chunk: the kept DFT_{N_out} slots of every row (scaled),
-// placed at their bins of an N-point row, then N-point inverse transforms.
-// N a power of two: placed in `dtmp` and transformed into `dense` (one pass),
-// or placed in `dense`, first pass into `dtmp`, second pass back into `dense`.
-// N = r * Md (r = 3, 5): the radix-r combination first (decimated rows
-// A_n1), then the Md-point transforms of the r rows, then the rows back to
-// the natural order:
-//   one pass:  place -> dtmp, radix -> dense, transform -> dtmp, permute -> dense;
-//   two passes: place -> dense, radix -> dtmp, pass 1 -> dense, pass 2 -> dtmp,
-//               permute -> dense.
+// then the N-point inverse transform of each row from its packed entries,
+// N = R * Md, decimated by R: in one launch where Md fits one workgroup, else
+// columns into `dtmp` and rows into the interleaved tiles.
+template <typename T, int R>
+bool dense_transform(qtam_plan_s* pl, const void* pack, void* dense, int64_t count, void* dtmp, hipStream_t st) {
+  using C = typename Complex<T>::type;
+  const HostPlan& hp = pl->hp;
+  const int64_t md = pl->dense_md;
+  if (!pl->dense_four_step) {
+    Timed tm(pl, K_DENSE_FFT, st);
+    switch (ilog2(md)) {
+#define X(LG)                                                                                           \
+  case LG:                                                                                              \
+    if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Single32 : kMaxLog2Single64)) {                     \
+      using Geo = RowGeom<T, (1 << LG)>;                                                                \
+      hipLaunchKernelGGL((k_dense_rows<T, (1 << LG), R>), dim3(unsigned((count + Geo::G - 1) / Geo::G * R)), \
+                         dim3(Geo::NT), 0, st, static_cast<const C*>(pack), static_cast<C*>(dense), pl->d_rows, \
+                         hp.rows, count, int64_t(hp.sum_len), static_cast<const C*>(pl->d_tw_dense), tw2_of<T>(pl)); \
+      return true;                                                                                      \
+    }                                                                                                   \
+    return false;
+      QTAM_POW2_CASES(X)
+#undef X
+      default: return false;
+    }
+  }
+  bool ok = false;
+  {
+    Timed tm(pl, K_DENSE_FFT1, st);
+    switch (ilog2(pl->dn2)) {
+#define X(LG)                                                                                           \
+  case LG:                                                                                              \
+    if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Col32 : kMaxLog2Col64)) {                           \
+      using Geo = ColGeom<T, (1 << LG)>;                                                                \
+      if (pl->dn1 % Geo::CC) return false;                                                              \
+      hipLaunchKernelGGL((k_dense_cols<T, (1 << LG), R>), dim3(unsigned(pl->dn1 / Geo::CC), unsigned(count * R)), \
+                         dim3(Geo::NT), 0, st, static_cast<const C*>(pack), static_cast<C*>(dtmp), pl->d_rows, \
+                         hp.rows, int64_t(hp.sum_len), md, pl->dn1, static_cast<const C*>(pl->d_tw_dn2), tw2_of<T>(pl)); \
+      ok = true;                                                                                        \
+    }                                                                                                   \
+    break;
+      QTAM_COL_CASES(X)
+#undef X
+      default: break;
+    }
+  }
+  if (!ok) return false;
+  Timed tm(pl, K_DENSE_FFT2, st);
+  return launch_fft_rows_t<T, +1, 0, R>(ilog2(pl->dn1), dtmp, dense, pl->dn2, count * R, md, pl->d_tw_dn1, st);
+}
+
 template <typename T>
 bool run_dense(qtam_plan_s* pl, const void* y, void* dense, int64_t segs, char* ws, const WsLayout& lay, void* dtmp,
                hipStream_t st) {
-  using C = typename Complex<T>::type;
-  const HostPlan& hp = pl->hp;
   if (!inverse_rows<T>(pl, T_DENSE, y, segs, ws, lay, st)) return false;
-  const int64_t count = segs * hp.rows;
-  const int r = pl->radix_r;
-  const int64_t md = pl->dense_md;
-  {
-    Timed tm(pl, K_DENSE_PLACE, st);
-    hipLaunchKernelGGL((k_place<T>), dim3(unsigned((hp.n + 255) / 256), unsigned(count)), dim3(256), 0, st,
-                       static_cast<const C*>(static_cast<void*>(ws + lay.pack)),
-                       static_cast<C*>(pl->dense_four_step ? dense : dtmp), pl->d_rows, hp.rows, hp.n, hp.sum_len);
-  }
-  // the buffer holding the placed rows, and the other one
-  void* a = pl->dense_four_step ? dense : dtmp;
-  void* b = pl->dense_four_step ? dtmp : dense;
-  if (r > 1) {
-    Timed tm(pl, K_DENSE_RADIX, st);
-    const dim3 grid(unsigned((md + 255) / 256), unsigned(count));
-    if (r == 3)
-      hipLaunchKernelGGL((k_radix<T, 3, 1>), grid, dim3(256), 0, st, static_cast<const C*>(a),
-                         static_cast<C*>(b), md, tw2_of<T>(pl));
-    else if (r == 5)
-      hipLaunchKernelGGL((k_radix<T, 5, 1>), grid, dim3(256), 0, st, static_cast<const C*>(a),
-                         static_cast<C*>(b), md, tw2_of<T>(pl));
-    else
-      return false;
-    std::swap(a, b);
-  }
-  // Md-point transforms of the rows in `a`, result in `b`
-  const int64_t rows = count * r;
-  bool ok;
-  if (!pl->dense_four_step) {
-    Timed tm(pl, K_DENSE_FFT, st);
-    ok = launch_fft_rows<T, +1>(ilog2(md), a, b, rows, md, pl->d_tw_dense, st);
-  } else {
-    {
-      Timed tm(pl, K_DENSE_FFT1, st);
-      ok = launch_fft_cols<T, +1>(ilog2(pl->dn2), a, b, pl->dn1, rows, md, pl->d_tw_dn2, tw2_of<T>(pl), st, r);
-    }
-    if (ok) {
-      Timed tm(pl, K_DENSE_FFT2, st);
-      ok = launch_fft_rows_t<T, +1>(ilog2(pl->dn1), b, a, pl->dn2, rows, md, pl->d_tw_dn1, st);
-    }
-    std::swap(a, b);
-  }
-  if (!ok || r == 1) return ok;
-  Timed tm(pl, K_DENSE_PERM, st);
-  hipLaunchKernelGGL((k_permute<T>), dim3(unsigned((hp.n + 255) / 256), unsigned(count)), dim3(256), 0, st,
-                     static_cast<const C*>(b), static_cast<C*>(a), r, md);
-  return true;
+  const int64_t count = segs * pl->hp.rows;
+  const void* pack = ws + lay.pack;
+  return pl->radix_r == 3   ? dense_transform<T, 3>(pl, pack, dense, count, dtmp, st)
+         : pl->radix_r == 5 ? dense_transform<T, 5>(pl, pack, dense, count, dtmp, st)
+                            : dense_transform<T, 1>(pl, pack, dense, count, dtmp, st);
 }
 
 // Segments per dense chunk: rows index grid.y, each chunk's tiles below 2 GiB.

@@ -11,21 +11,123 @@
 
 namespace qtam {
 
-// Dense tiles: row k of segment s as an N-point spectrum holding its packed
-// kept entries at their bins lo..hi and zeros elsewhere (the inverse FFT of
-// that row is the dense tile). One thread per output bin, rows in grid.y.
-template <typename T>
-__global__ __launch_bounds__(256) void k_place(const typename Complex<T>::type* __restrict__ Sbuf,
-                                               typename Complex<T>::type* __restrict__ D, const RowMeta* __restrict__ rows,
-                                               int R, int64_t n, int64_t sum_len) {
+// Dense tiles: row k of segment s is the N-point inverse transform of its
+// packed kept entries at their bins lo..hi (zeros elsewhere), N = R * Md.
+// Decimated by R: T[n1 + R n2] = IDFT_Md(A_n1)[n2], A_n1[k] = sum over the
+// bins c = k mod Md of Z[c] e^{+2 pi i n1 c / N} (one bin, or a few where the
+// support is wider than Md). The values k = index(i), i < E, of sibling n1 of
+// a row, straight from its packed entries: r a resource over the len of them
+// (the entry of bin c at c - lo; beyond it reads 0), the same for the wave.
+template <typename T, int E, typename Index>
+__device__ __forceinline__ void dense_values(typename Complex<T>::type (&v)[E], Index&& index, rsrc_t r, int64_t md,
+                                             int n1, int lo, int len, int64_t n,
+                                             const Twiddle2<typename Complex<T>::type>& tw2) {
   using C = typename Complex<T>::type;
-  const int64_t b = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (b >= n) return;
-  const int64_t gr = blockIdx.y;
-  const int64_t seg = gr / R;
-  const RowMeta rm = rows[gr - seg * R];
-  const bool in = b >= rm.lo && b <= rm.hi;
-  D[gr * n + b] = in ? Sbuf[seg * sum_len + rm.off + (b - rm.lo)] : C{0, 0};
+  const unsigned nn = static_cast<unsigned>(n);
+  auto root = [&](unsigned d) {   // e^{+2 pi i n1 (lo + d) / N}; n1 (lo + d) < 4 N
+    unsigned m = static_cast<unsigned>(n1) * (static_cast<unsigned>(lo) + d);
+    if (m >= 2 * nn) m -= 2 * nn;
+    if (m >= nn) m -= nn;
+    return c_conj(tw2(m));
+  };
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+    v[i] = bload<C>(r, (static_cast<unsigned>(index(i) - lo) & static_cast<unsigned>(md - 1)) * sizeof(C));
+  if (n1 > 0) {
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+      v[i] = c_mul(v[i], root(static_cast<unsigned>(index(i) - lo) & static_cast<unsigned>(md - 1)));
+  }
+  for (int more = static_cast<int>(md); more < len; more += static_cast<int>(md)) {   // supports wider than Md
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const unsigned d = (static_cast<unsigned>(index(i) - lo) & static_cast<unsigned>(md - 1)) + more;
+      if (d < static_cast<unsigned>(len)) {
+        const C z = bload<C>(r, d * static_cast<unsigned>(sizeof(C)));
+        v[i] = c_add(v[i], n1 > 0 ? c_mul(z, root(d)) : z);
+      }
+    }
+  }
+}
+
+// Md in one workgroup: packed entries to the finished tile, one launch. The R
+// siblings of a row write its interleaved values from one XCD. Bound by the
+// write of the tiles. Measured on MI355X, FP32, 16 x 24576 samples, 62 rows
+// (R = 3, 195 MB of tiles), forward + dense: 306 us with placing, radix pass,
+// transforms and permutation as passes of their own, 123 us with this kernel;
+// 16 x 16384 samples (R = 1) 126 to 81 us.
+template <typename T, int L, int R>
+__global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_dense_rows(
+    const typename Complex<T>::type* __restrict__ Sbuf, typename Complex<T>::type* __restrict__ D,
+    const RowMeta* __restrict__ rows, int nrows, int64_t count, int64_t sum_len,
+    const typename Complex<T>::type* __restrict__ tw, Twiddle2<typename Complex<T>::type> tw2) {
+  using C = typename Complex<T>::type;
+  using Geo = RowGeom<T, L>;
+  using F = BlockFft<T, L, Geo::E, +1>;
+  __shared__ C lds[Geo::G * lds_size(L)];
+  const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
+  int64_t u = blockIdx.x;
+  int n1 = 0;
+  if constexpr (R > 1) sibling_block<R>(blockIdx.x, gridDim.x / R, u, n1);
+  int gr = static_cast<int>(u) * Geo::G + g;
+  if constexpr (Geo::TPR >= 64) gr = __builtin_amdgcn_readfirstlane(gr);
+  const bool ok = gr < count;
+  const int seg = ok ? gr / nrows : 0;
+  const RowMeta rm = rows[ok ? gr - seg * nrows : 0];
+  const int len = ok ? rm.hi - rm.lo + 1 : 0;
+  const C* src = Sbuf + int64_t(seg) * sum_len + rm.off;
+  C v[Geo::E];
+  if constexpr (Geo::TPR >= 64) {
+    dense_values<T>(v, [&](int i) { return tl + F::in_off(i); }, make_rsrc(src, static_cast<uint32_t>(len * sizeof(C))),
+                    L, n1, rm.lo, len, int64_t(R) * L, tw2);
+  } else {   // several rows per wave
+#pragma unroll
+    for (int i = 0; i < Geo::E; ++i) {
+      v[i] = C{0, 0};
+      for (int d = (tl + F::in_off(i) - rm.lo) & (L - 1); d < len; d += L) {
+        const C z = src[d];
+        v[i] = c_add(v[i], n1 > 0 ? c_mul(z, c_conj(tw2(n1 * (rm.lo + d) % (R * L)))) : z);
+      }
+    }
+  }
+  F::run(v, lds + g * lds_size(L), tl, F::twiddles(tw));
+  if (!ok) return;
+  C* dst = D + int64_t(gr) * (R * L) + n1 + R * tl;
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) dst[R * F::out_off(i)] = v[i];
+}
+
+// Md = L1 * L2 in two passes: this column pass (as k_fft_cols over the values
+// above, into the workspace), then k_fft_rows_t, which writes the interleaved
+// tile. blockIdx.y = row * R + n1. Measured, 64 rows, FP32, forward + dense:
+// 4 x 131072 samples (R = 1) 396 to 300 us, 4 x 98304 (R = 3) 433 to 255 us.
+template <typename T, int L2, int R>
+__global__ __launch_bounds__((ColGeom<T, L2>::NT)) void k_dense_cols(
+    const typename Complex<T>::type* __restrict__ Sbuf, typename Complex<T>::type* __restrict__ A,
+    const RowMeta* __restrict__ rows, int nrows, int64_t sum_len, int64_t md, int64_t l1,
+    const typename Complex<T>::type* __restrict__ tw, Twiddle2<typename Complex<T>::type> tw2) {
+  using C = typename Complex<T>::type;
+  using Geo = ColGeom<T, L2>;
+  using F = BlockFft<T, L2, Geo::E, +1>;
+  __shared__ C lds[Geo::CC * lds_size(L2)];
+  const int t = threadIdx.x, cc = t % Geo::CC, tl = t / Geo::CC;
+  const int64_t c1 = int64_t(blockIdx.x) * Geo::CC + cc;
+  const int64_t gr = blockIdx.y / R;
+  const int n1 = blockIdx.y % R;
+  const int64_t seg = gr / nrows;
+  const RowMeta rm = rows[gr - seg * nrows];
+  const int len = rm.hi - rm.lo + 1;
+  C v[Geo::E];
+  dense_values<T>(v, [&](int i) { return static_cast<int>(c1 + l1 * F::in_index(tl, i)); },
+                  make_rsrc(Sbuf + seg * sum_len + rm.off, static_cast<uint32_t>(len * sizeof(C))), md, n1, rm.lo, len,
+                  R * md, tw2);
+  F::run(v, lds + cc * lds_size(L2), tl, F::twiddles(tw));
+  C* dst = A + int64_t(blockIdx.y) * md + c1;
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) {
+    const int64_t k2 = F::out_index(tl, i);
+    dst[l1 * k2] = c_mul(v[i], c_conj(tw2(R * c1 * k2)));   // exp(+2 pi i c1 k2 / Md)
+  }
 }
 
 // Single-tile recovery: row `row` of each segment, its N_out-point forward

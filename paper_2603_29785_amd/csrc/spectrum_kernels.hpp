@@ -26,11 +26,10 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_fft_rows(
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   int64_t tr0 = int64_t(blockIdx.x) * Geo::G;
   if constexpr (RIN * ROUT > 1) {
-    // workgroups go round-robin over the 8 XCDs: the r siblings of a segment,
-    // which share its lines, take workgroups a multiple of 8 apart (one L2)
-    constexpr int r = RIN * ROUT;
-    const int64_t s0 = tr0 / (8 * r) * 8, m = count / r - s0 < 8 ? count / r - s0 : 8, k = tr0 - s0 * r;
-    tr0 = (s0 + k % m) * r + k / m;
+    int64_t v;
+    int s;
+    sibling_block<RIN * ROUT>(tr0, count / (RIN * ROUT), v, s);
+    tr0 = v * (RIN * ROUT) + s;
   }
   const int64_t nt = count - tr0 < Geo::G ? count - tr0 : Geo::G;   // transforms of this block
   const uint32_t bytes = static_cast<uint32_t>((nt - 1) * stride + L) * sizeof(C);
@@ -67,9 +66,17 @@ __global__ __launch_bounds__((ColGeom<T, L, 0, CW>::NT)) void k_fft_cols(
   using F = BlockFft<T, L, Geo::E, S>;
   __shared__ C lds[Geo::CC * lds_size(L)];
   const int t = threadIdx.x, c = t % Geo::CC, tl = t / Geo::CC;
-  const int64_t n1 = int64_t(blockIdx.x) * Geo::CC + c;
-  const int64_t base = int64_t(blockIdx.y) * seg_stride + n1;
-  const int64_t bin = RIN > 1 ? int64_t(blockIdx.y / RIN) * RIN * seg_stride + blockIdx.y % RIN + RIN * n1 : base;
+  int64_t bx = blockIdx.x, by = blockIdx.y;   // column tile, transform
+  int sib = 0;
+  if constexpr (RIN > 1) {
+    int64_t v;
+    sibling_block<RIN>(by * gridDim.x + bx, int64_t(gridDim.x) * (gridDim.y / RIN), v, sib);
+    bx = v % gridDim.x;
+    by = v / gridDim.x * RIN + sib;
+  }
+  const int64_t n1 = bx * Geo::CC + c;
+  const int64_t base = by * seg_stride + n1;
+  const int64_t bin = RIN > 1 ? (by - sib) * seg_stride + sib + RIN * n1 : base;
   C v[Geo::E];
 #pragma unroll
   for (int i = 0; i < Geo::E; ++i) v[i] = in[bin + RIN * n1_count * F::in_index(tl, i)];
@@ -98,8 +105,16 @@ __global__ __launch_bounds__((ColGeom<T, L, EP, CW>::NT)) void k_fft_rows_t(
   using F = BlockFft<T, L, Geo::E, S>;
   __shared__ C lds[Geo::CC * lds_size(L)];
   const int t = threadIdx.x;
-  const int64_t k2_0 = int64_t(blockIdx.x) * Geo::CC;
-  const C* src = in + int64_t(blockIdx.y) * seg_stride + k2_0 * L;
+  int64_t bx = blockIdx.x, by = blockIdx.y;   // row tile, transform
+  int sib = 0;
+  if constexpr (ROUT > 1) {
+    int64_t v;
+    sibling_block<ROUT>(by * gridDim.x + bx, int64_t(gridDim.x) * (gridDim.y / ROUT), v, sib);
+    bx = v % gridDim.x;
+    by = v / gridDim.x * ROUT + sib;
+  }
+  const int64_t k2_0 = bx * Geo::CC;
+  const C* src = in + by * seg_stride + k2_0 * L;
   for (int i = t; i < Geo::CC * L; i += Geo::NT) lds[(i / L) * lds_size(L) + lds_pad(i % L)] = src[i];
   __syncthreads();
   const int c = t % Geo::CC, tl = t / Geo::CC;
@@ -109,8 +124,7 @@ __global__ __launch_bounds__((ColGeom<T, L, EP, CW>::NT)) void k_fft_rows_t(
   for (int i = 0; i < Geo::E; ++i) v[i] = reg[lds_pad(F::in_index(tl, i))];
   __syncthreads();
   F::run(v, reg, tl, F::twiddles(tw));
-  C* dst = ROUT > 1 ? out + int64_t(blockIdx.y / ROUT) * ROUT * seg_stride + blockIdx.y % ROUT + ROUT * (k2_0 + c)
-                    : out + int64_t(blockIdx.y) * seg_stride + k2_0 + c;
+  C* dst = out + (by - sib) * seg_stride + sib + ROUT * (k2_0 + c);
 #pragma unroll
   for (int i = 0; i < Geo::E; ++i) dst[ROUT * n2_count * F::out_index(tl, i)] = v[i];
 }
@@ -189,21 +203,7 @@ __global__ __launch_bounds__((ColGeom<T, L, EP, CW>::NT)) void k_spec_rows_twist
 // synthesis pass writes the interleaved one, so no pass only permutes;
 // k_radix does the combination of the synthesis, k_radix_twist that of the
 // analysis with the real-signal twist, and where a segment fits one workgroup
-// k_spec_seg / k_syn_seg do all of it. k_permute moves dense tiles from the
-// decimated rows Zp[n1][n2] to the natural order z[n]. The same split serves
-// full-length transforms of N = r * M points (the dense tiles): then the
-// twiddles are e^{-+2 pi i n1 k2 / N}, one step of the N-point table per unit
-// of n1 k2 (TSTEP = 1) instead of two.
-template <typename T>
-__global__ __launch_bounds__(256) void k_permute(const typename Complex<T>::type* __restrict__ in,
-                                                 typename Complex<T>::type* __restrict__ out, int r, int64_t m2) {
-  const int64_t half = r * m2;
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;   // index in the decimated rows
-  if (i >= half) return;
-  const int64_t n1 = i / m2, n2 = i - n1 * m2;
-  const int64_t base = int64_t(blockIdx.y) * half;
-  out[base + n1 + r * n2] = in[base + i];
-}
+// k_spec_seg / k_syn_seg do all of it.
 
 // cos / sin of 2 pi k / R for R = 1, 3, 5
 template <typename T, int R>
@@ -237,9 +237,9 @@ __device__ __forceinline__ void dft_r(const typename Complex<T>::type (&a)[R], t
   }
 }
 
-// Radix-R combination of a synthesis (or of dense tiles): the spectrum Z to
-// the decimated rows A_n1, in rows of m2.
-template <typename T, int R, int TSTEP = 2>
+// Radix-R combination of a synthesis: the spectrum Z to the decimated rows
+// A_n1, in rows of m2.
+template <typename T, int R>
 __global__ __launch_bounds__(256) void k_radix(const typename Complex<T>::type* __restrict__ in,
                                                typename Complex<T>::type* __restrict__ out, int64_t m2,
                                                Twiddle2<typename Complex<T>::type> tw2) {
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(256) void k_radix(const typename Complex<T>::type* 
   dft_r<T, R, +1>(a, b);
 #pragma unroll
   for (int n1 = 0; n1 < R; ++n1)
-    out[base + n1 * m2 + k2] = n1 == 0 ? b[0] : c_mul(b[n1], c_conj(tw2(TSTEP * n1 * k2)));
+    out[base + n1 * m2 + k2] = n1 == 0 ? b[0] : c_mul(b[n1], c_conj(tw2(2 * n1 * k2)));
 }
 
 // Real-signal spectrum from the N/2-point transform Z of the even/odd pairs
