@@ -22,6 +22,13 @@
 // through the caches. Direction S = -1 computes sum_n a_n e^{-2 pi i nk/L},
 // S = +1 the unnormalised inverse kernel e^{+2 pi i nk/L} (conjugated
 // twiddles).
+// Arithmetic: twiddles and rotations are applied inside the butterflies' fused
+// multiply-adds and LDS offsets are one address plus constants; against
+// rounding each product first and one address per element this takes 733
+// vector instructions in the 4096-point inverse rows kernel where it took 896,
+// with slightly smaller errors. It bought 1 to 2.5% (256 x 131072 samples,
+// three Q: 3.91 to 3.85 ms; 32 x 2^21: 4.25 to 4.16 ms): these kernels wait
+// for memory and barriers as much as for the vector ALU.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -46,47 +53,57 @@ __device__ __forceinline__ double fmadd(double a, double b, double c) { return _
 template <typename C> __device__ __forceinline__ C c_mul(C a, C b) {
   return C{fmadd(a.x, b.x, -(a.y * b.y)), fmadd(a.x, b.y, a.y * b.x)};
 }
-template <typename C, typename T> __device__ __forceinline__ C c_scale(C a, T s) { return C{a.x * s, a.y * s}; }
 // a * (S i): S = +1 multiplies by i, S = -1 by -i
 template <int S, typename C> __device__ __forceinline__ C c_mul_si(C a) {
   if constexpr (S > 0) return C{-a.y, a.x};
   else return C{a.y, -a.x};
 }
 
-// cos and sin of 2 pi k / 16, k = 0..4 (the rest follow by symmetry)
-struct Root16 {
-  static constexpr double c1 = 0.92387953251128675613;
-  static constexpr double s1 = 0.38268343236508977173;
-  static constexpr double r2 = 0.70710678118654752440;
-};
+// acc + s v and acc + s (S i) v with a real scale s
+template <typename C, typename T> __device__ __forceinline__ C c_fma_s(C acc, C v, T s) {
+  return C{fmadd(v.x, s, acc.x), fmadd(v.y, s, acc.y)};
+}
+template <int S, typename C, typename T> __device__ __forceinline__ C c_fma_si(C acc, C v, T s) {
+  constexpr T g = static_cast<T>(S);
+  return C{fmadd(v.y, -g * s, acc.x), fmadd(v.x, g * s, acc.y)};
+}
+// acc + a w, and 2 q - t (t = q + p gives q - p: two fused multiply-adds for
+// the second output of a butterfly whose product p was never formed)
+template <typename C> __device__ __forceinline__ C c_fma(C acc, C a, C w) {
+  return C{fmadd(a.x, w.x, fmadd(-a.y, w.y, acc.x)), fmadd(a.x, w.y, fmadd(a.y, w.x, acc.y))};
+}
+template <typename C> __device__ __forceinline__ C c_twice_minus(C q, C t) {
+  using T = decltype(q.x);
+  return C{fmadd(T(2), q.x, -t.x), fmadd(T(2), q.y, -t.y)};
+}
 
-// a * exp(S 2 pi i k / 16) for a compile-time k
-template <int S, int K, typename C>
-__device__ __forceinline__ C c_mul_root16(C a) {
+// Rotations by exp(S 2 pi i k / 16) up to a real scale that the following
+// butterfly applies in its fused multiply-adds: k = 2 and 6 with scale
+// sqrt(1/2) (c_rot45, c_rot135), k = 1 with scale cos(pi/8) (c_rot22), k = 3
+// with the same scale (c_rot67), k = 9 with its negative.
+struct Root16 {
+  static constexpr double c1 = 0.92387953251128675613;   // cos(pi/8)
+  static constexpr double t1 = 0.41421356237309504880;   // tan(pi/8)
+  static constexpr double r2 = 0.70710678118654752440;   // sqrt(1/2)
+};
+template <int S, typename C> __device__ __forceinline__ C c_rot45(C a) {
+  if constexpr (S > 0) return C{a.x - a.y, a.y + a.x};
+  else return C{a.x + a.y, a.y - a.x};
+}
+template <int S, typename C> __device__ __forceinline__ C c_rot135(C a) {
+  if constexpr (S > 0) return C{-a.x - a.y, a.x - a.y};
+  else return C{a.y - a.x, -a.x - a.y};
+}
+template <int S, typename C> __device__ __forceinline__ C c_rot22(C a) {
   using T = decltype(a.x);
-  constexpr int k = ((K % 16) + 16) % 16;
-  if constexpr (k == 0) return a;
-  else if constexpr (k == 4) return c_mul_si<S>(a);
-  else if constexpr (k == 8) return C{-a.x, -a.y};
-  else if constexpr (k == 12) return c_mul_si<-S>(a);
-  else if constexpr (k == 2 || k == 6 || k == 10 || k == 14) {
-    // exp(S i pi/4 * k/2) = (cx + i sy) / sqrt 2, cx, sy in {+1, -1}
-    constexpr T r = static_cast<T>(Root16::r2);
-    constexpr bool cpos = (k == 2 || k == 14);
-    constexpr bool spos = (k == 2 || k == 6) == (S > 0);
-    const T re = cpos ? (spos ? a.x - a.y : a.x + a.y) : (spos ? -a.x - a.y : a.y - a.x);
-    const T im = cpos ? (spos ? a.x + a.y : a.y - a.x) : (spos ? a.x - a.y : -a.x - a.y);
-    return C{re * r, im * r};
-  } else {
-    // k odd: cos / sin of 2 pi k/16 from the first-octant values
-    constexpr int m = k % 8;                     // reduce by pi
-    constexpr T sg = k >= 8 ? T(-1) : T(1);
-    constexpr T cs = static_cast<T>(m == 1 ? Root16::c1 : m == 3 ? Root16::s1 : m == 5 ? -Root16::s1 : -Root16::c1);
-    constexpr T sn = static_cast<T>(m == 1 ? Root16::s1 : m == 3 ? Root16::c1 : m == 5 ? Root16::c1 : Root16::s1);
-    constexpr T cx = sg * cs;
-    constexpr T sy = sg * sn * static_cast<T>(S);
-    return C{fmadd(a.x, cx, -(a.y * sy)), fmadd(a.x, sy, a.y * cx)};
-  }
+  constexpr T t = static_cast<T>(S * Root16::t1);
+  return C{fmadd(a.y, -t, a.x), fmadd(a.x, t, a.y)};
+}
+template <int S, typename C> __device__ __forceinline__ C c_rot67(C a) {
+  using T = decltype(a.x);
+  constexpr T t = static_cast<T>(Root16::t1);
+  if constexpr (S > 0) return C{fmadd(a.x, t, -a.y), fmadd(a.y, t, a.x)};
+  else return C{fmadd(a.x, t, a.y), fmadd(a.y, t, -a.x)};
 }
 
 template <int S, typename C>
@@ -106,29 +123,56 @@ __device__ __forceinline__ void dft4(C& a0, C& a1, C& a2, C& a3) {
   a3 = c_sub(t1, t3);
 }
 
+// Length-4 DFT whose inputs 1..3 (or 0..3) still take their twiddles: the
+// products go into the butterflies' fused multiply-adds, 24 (28) operations
+// where multiplying first takes 28 (32).
+template <int S, bool FIRST, typename C>
+__device__ __forceinline__ void dft4_tw(C& a0, C& a1, C& a2, C& a3, C w0, C w1, C w2, C w3) {
+  if constexpr (FIRST) a0 = c_mul(a0, w0);
+  const C t0 = c_fma(a0, a2, w2), t1 = c_twice_minus(a0, t0);
+  const C q = c_mul(a1, w1);
+  const C t2 = c_fma(q, a3, w3), t3 = c_mul_si<S>(c_twice_minus(q, t2));
+  a0 = c_add(t0, t2);
+  a2 = c_sub(t0, t2);
+  a1 = c_add(t1, t3);
+  a3 = c_sub(t1, t3);
+}
+
 // Second half of a radix-16 DFT split as n = 4 n1 + n2: group n2's output
 // k1 sits at a[4 k1 + n2]; twiddles exp(S 2 pi i n2 k1 / 16), then the outer
-// length-4 DFTs over the groups, results in natural order.
+// length-4 DFTs over the groups, results in natural order. The rotations keep
+// their scales for the last additions (80 operations; 96 when each product is
+// rounded first).
 template <int S, typename C>
 __device__ __forceinline__ void dft16_outer(C* a) {
-  a[5] = c_mul_root16<S, 1>(a[5]);
-  a[9] = c_mul_root16<S, 2>(a[9]);
-  a[13] = c_mul_root16<S, 3>(a[13]);
-  a[6] = c_mul_root16<S, 2>(a[6]);
-  a[10] = c_mul_root16<S, 4>(a[10]);
-  a[14] = c_mul_root16<S, 6>(a[14]);
-  a[7] = c_mul_root16<S, 3>(a[7]);
-  a[11] = c_mul_root16<S, 6>(a[11]);
-  a[15] = c_mul_root16<S, 9>(a[15]);
+  using T = decltype(a[0].x);
+  constexpr T c1 = static_cast<T>(Root16::c1), r2 = static_cast<T>(Root16::r2);
   C y[16];
-#pragma unroll
-  for (int k1 = 0; k1 < 4; ++k1) {
-    C b0 = a[4 * k1], b1 = a[4 * k1 + 1], b2 = a[4 * k1 + 2], b3 = a[4 * k1 + 3];
+  auto last = [&](int k1, C t0, C t1, C t2, C t3, T s) {   // t2, t3 up to the scale s
+    y[k1] = c_fma_s(t0, t2, s);
+    y[k1 + 8] = c_fma_s(t0, t2, -s);
+    y[k1 + 4] = c_fma_si<S>(t1, t3, s);
+    y[k1 + 12] = c_fma_si<S>(t1, t3, -s);
+  };
+  {
+    C b0 = a[0], b1 = a[1], b2 = a[2], b3 = a[3];
     dft4<S>(b0, b1, b2, b3);
-    y[k1] = b0;
-    y[k1 + 4] = b1;
-    y[k1 + 8] = b2;
-    y[k1 + 12] = b3;
+    y[0] = b0;
+    y[4] = b1;
+    y[8] = b2;
+    y[12] = b3;
+  }
+  {
+    const C u = c_rot45<S>(a[6]), p1 = c_rot22<S>(a[5]), p3 = c_rot67<S>(a[7]);
+    last(1, c_fma_s(a[4], u, r2), c_fma_s(a[4], u, -r2), c_add(p1, p3), c_sub(p1, p3), c1);
+  }
+  {
+    const C b2 = c_mul_si<S>(a[10]), u1 = c_rot45<S>(a[9]), u3 = c_rot135<S>(a[11]);
+    last(2, c_add(a[8], b2), c_sub(a[8], b2), c_add(u1, u3), c_sub(u1, u3), r2);
+  }
+  {
+    const C u = c_rot135<S>(a[14]), p1 = c_rot67<S>(a[13]), p3 = c_rot22<S>(a[15]);   // p3 with scale -c1
+    last(3, c_fma_s(a[12], u, r2), c_fma_s(a[12], u, -r2), c_sub(p1, p3), c_add(p1, p3), c1);
   }
 #pragma unroll
   for (int i = 0; i < 16; ++i) a[i] = y[i];
@@ -163,24 +207,36 @@ __device__ __forceinline__ void dft16_sparse(C* a) {
     from_last(2);
     dft16_outer<S>(a);
   } else {
-    // groups 1 and 2 are zero: twiddles only on group 3, and each outer
-    // length-4 DFT sees (b0, 0, 0, b3)
-    a[7] = c_mul_root16<S, 3>(a[7]);
-    a[11] = c_mul_root16<S, 6>(a[11]);
-    a[15] = c_mul_root16<S, 9>(a[15]);
+    // groups 1 and 2 are zero: each outer length-4 DFT sees (b0, 0, 0, b3)
+    using T = decltype(a[0].x);
+    constexpr T c1 = static_cast<T>(Root16::c1), r2 = static_cast<T>(Root16::r2);
     C y[16];
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) {
-      const C b0 = a[4 * k1], b3 = a[4 * k1 + 3];
-      const C t3 = c_mul_si<S>(C{-b3.x, -b3.y});
-      y[k1] = c_add(b0, b3);
-      y[k1 + 4] = c_add(b0, t3);
-      y[k1 + 8] = c_sub(b0, b3);
-      y[k1 + 12] = c_sub(b0, t3);
-    }
+    auto last = [&](int k1, C b0, C p, T s) {   // b3 times its root = s p
+      y[k1] = c_fma_s(b0, p, s);
+      y[k1 + 8] = c_fma_s(b0, p, -s);
+      y[k1 + 4] = c_fma_si<S>(b0, p, -s);
+      y[k1 + 12] = c_fma_si<S>(b0, p, s);
+    };
+    last(0, a[0], a[3], T(1));
+    last(1, a[4], c_rot67<S>(a[7]), c1);
+    last(2, a[8], c_rot135<S>(a[11]), r2);
+    last(3, a[12], c_rot22<S>(a[15]), -c1);
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[i] = y[i];
   }
+}
+
+// Second half of a radix-8 DFT split as n = 2 n1 + n2: group n2's output k1
+// sits at a[2 k1 + n2].
+template <int S, typename C>
+__device__ __forceinline__ void dft8_outer(C* a) {
+  using T = decltype(a[0].x);
+  constexpr T r2 = static_cast<T>(Root16::r2);
+  const C u1 = c_rot45<S>(a[3]), u2 = c_mul_si<S>(a[5]), u3 = c_rot135<S>(a[7]);
+  const C y[8] = {c_add(a[0], a[1]),     c_fma_s(a[2], u1, r2),  c_add(a[4], u2), c_fma_s(a[6], u3, r2),
+                  c_sub(a[0], a[1]),     c_fma_s(a[2], u1, -r2), c_sub(a[4], u2), c_fma_s(a[6], u3, -r2)};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = y[i];
 }
 
 // In-register DFT of R values in natural order (R in 1, 2, 4, 8, 16).
@@ -197,19 +253,7 @@ __device__ __forceinline__ void dft_small(C* a) {
     // n = 2 n1 + n2, k = k1 + 4 k2
     dft4<S>(a[0], a[2], a[4], a[6]);
     dft4<S>(a[1], a[3], a[5], a[7]);
-    a[3] = c_mul_root16<S, 2>(a[3]);
-    a[5] = c_mul_root16<S, 4>(a[5]);
-    a[7] = c_mul_root16<S, 6>(a[7]);
-    C y[8];
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) {
-      C e = a[2 * k1], o = a[2 * k1 + 1];
-      dft2<S>(e, o);
-      y[k1] = e;
-      y[k1 + 4] = o;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = y[i];
+    dft8_outer<S>(a);
   } else if constexpr (R == 16) {
     // n = 4 n1 + n2: group n2 holds a[n2], a[4+n2], a[8+n2], a[12+n2]
     dft4<S>(a[0], a[4], a[8], a[12]);
@@ -220,11 +264,36 @@ __device__ __forceinline__ void dft_small(C* a) {
   }
 }
 
+// The same of a[r] w[r] (w[0] is 1 and not read).
+template <int S, int R, typename C>
+__device__ __forceinline__ void dft_small_tw(C* a, const C* w) {
+  if constexpr (R == 2) {
+    const C t = c_fma(a[0], a[1], w[1]);
+    a[1] = c_twice_minus(a[0], t);
+    a[0] = t;
+  } else if constexpr (R == 4) {
+    dft4_tw<S, false>(a[0], a[1], a[2], a[3], C{}, w[1], w[2], w[3]);
+  } else if constexpr (R == 8) {
+    dft4_tw<S, false>(a[0], a[2], a[4], a[6], C{}, w[2], w[4], w[6]);
+    dft4_tw<S, true>(a[1], a[3], a[5], a[7], w[1], w[3], w[5], w[7]);
+    dft8_outer<S>(a);
+  } else {
+    static_assert(R == 16, "radices 2, 4, 8, 16");
+    dft4_tw<S, false>(a[0], a[4], a[8], a[12], C{}, w[4], w[8], w[12]);
+    dft4_tw<S, true>(a[1], a[5], a[9], a[13], w[1], w[5], w[9], w[13]);
+    dft4_tw<S, true>(a[2], a[6], a[10], a[14], w[2], w[6], w[10], w[14]);
+    dft4_tw<S, true>(a[3], a[7], a[11], a[15], w[3], w[7], w[11], w[15]);
+    dft16_outer<S>(a);
+  }
+}
+
 // LDS index with one pad element every 32, which spreads power-of-two strides
 // over the banks; the map is affine inside each run of 32, so exchanges keep
 // constant instruction offsets.
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 5); }
 constexpr int lds_size(int l) { return l + l / 32 + 1; }
+// lds_pad(i + c) for a c that shares no bit with i: lds_pad(i) plus a constant
+constexpr int lds_step(int c) { return c + (c >> 5); }
 
 // Twiddle table layouts: TW_POW stores the base powers w^1, w^2, w^4, w^8 of
 // each pass and forms the others by products (little table traffic, for
@@ -341,14 +410,14 @@ struct BlockFft {
     for (int q = 0; q < E / R; ++q) {
       if constexpr (NS > 1) {
         if constexpr (!kAll) load_twiddles<NS>(w, tl, tw, q, q + 1);
+        C t[R];
 #pragma unroll
         for (int r = 1; r < R; ++r) {
-          C t = w[(kAll ? q * R : 0) + r];
-          if constexpr (S > 0) t.y = -t.y;
-          v[q * R + r] = c_mul(v[q * R + r], t);
+          t[r] = w[(kAll ? q * R : 0) + r];
+          if constexpr (S > 0) t[r].y = -t[r].y;
         }
-      }
-      if constexpr (NS == 1 && R == 16) {
+        dft_small_tw<S, R>(&v[q * R], t);
+      } else if constexpr (R == 16) {
         if (nz == 2) dft16_sparse<S, 2>(&v[q * R]);
         else if (nz == 4) dft16_sparse<S, 4>(&v[q * R]);
         else dft_small<S, R>(&v[q * R]);
@@ -364,16 +433,16 @@ struct BlockFft {
         for (int q = 0; q < E / R; ++q) {
           const int j = tl + q * TPR;
           const int k = j & (NS - 1);
-          const int base = (j - k) * R + k;
+          const int base = lds_pad((j - k) * R + k);   // no bit of r NS set
 #pragma unroll
-          for (int r = 0; r < R; ++r) lds[lds_pad(base + r * NS)] = v[q * R + r];
+          for (int r = 0; r < R; ++r) lds[base + lds_step(r * NS)] = v[q * R + r];
         }
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < E / R2; ++q) {
-          const int j = tl + q * TPR;
+          const int j = lds_pad(tl) + lds_step(q * TPR);   // tl < TPR, tl + q TPR < L / R2
 #pragma unroll
-          for (int r = 0; r < R2; ++r) v[q * R2 + r] = lds[lds_pad(j + r * (L / R2))];
+          for (int r = 0; r < R2; ++r) v[q * R2 + r] = lds[j + lds_step(r * (L / R2))];
         }
         __syncthreads();
       } else {
@@ -392,9 +461,9 @@ struct BlockFft {
           {
             const int j = tl + h * TPR;
             const int k = j & (NS - 1);
-            const int base = (j - k) * R + k - h * H;
+            const int base = lds_pad((j - k) * R + k - h * H);
 #pragma unroll
-            for (int r = 0; r < R; ++r) lds[lds_pad(base + r * NS)] = v[h * R + r];
+            for (int r = 0; r < R; ++r) lds[base + lds_step(r * NS)] = v[h * R + r];
           }
           __syncthreads();
           int n = 0;
@@ -404,7 +473,7 @@ struct BlockFft {
             for (int r = 0; r < R2; ++r) {
               const int off = q * TPR + r * (L / R2);   // compile-time after unrolling
               if ((off < H) == (h == 0)) {
-                const C x = lds[lds_pad(tl + off - h * H)];
+                const C x = lds[lds_pad(tl) + lds_step(off - h * H)];
                 if (h == 0) tmp[n++] = x;
                 else v[q * R2 + r] = x;
               }
