@@ -62,6 +62,38 @@ struct RowGeom {
   static constexpr int NT = G * TPR;
 };
 
+// Envelope rows of the row kernels. WIDE: twice the values per thread (two
+// groups of butterflies, exchanges in two rounds over half a region), so the
+// 128 registers and the LDS of a CU hold twice the rows and more of them load,
+// store or transform at any time. It takes enough rows to fill the chip twice
+// over: with fewer, the one-group form has twice the waves per row. The
+// butterflies are the same in both, so are the results, bit for bit.
+// Measured (MI355X, forward / inverse rows, us, one group : two groups):
+//   FP32 N_out  4096, 65536 rows 537/603 : 499/587;   2048 rows 21/24 : 22/24
+//   FP32 N_out  8192, 16384 rows 343/395 : 291/329;    512 rows 16/19 : 17/18
+//   FP32 N_out 16384,  8192 rows 416/465 : 326/372;    256 rows 20/20 : 21/21
+//   FP64 N_out  4096, 16384 rows 276/314 : 239/279;    512 rows 15/15 : 16/16
+//   FP64 N_out  8192,  8192 rows 386/414 : 325/358;    256 rows 20/18 : 20/20
+template <typename T, int L> constexpr bool wide_rows() {
+  return sizeof(T) == 4 ? L >= 2048 && L <= 16384 : L >= 1024 && L <= 8192;
+}
+// Envelope bytes of a launch from which rows take the two-group form: 64 MB
+// where one group leaves at most two rows per CU (rows of 64 KB and more), 256
+// MB where it leaves four (both forms within 3% of each other in between).
+constexpr int64_t wide_from_bytes(int64_t row_bytes) {
+  return row_bytes >= 65536 ? int64_t(64) << 20 : int64_t(256) << 20;
+}
+template <typename T, int L, bool WIDE = false>
+struct RowsGeom {
+  static constexpr int E = WIDE ? 2 * elems_per_thread<T>() : RowGeom<T, L>::E;
+  static constexpr int RM = WIDE ? elems_per_thread<T>() : (E < 16 ? E : 16);
+  static constexpr int TPR = L / E;
+  static constexpr int G = TPR >= 256 ? 1 : 256 / TPR;
+  static constexpr int NT = G * TPR;
+  static constexpr int LDS = WIDE ? lds_size(L / 2) : fft_lds_elems<T, L>();
+  template <int S> using Fft = BlockFft<T, L, E, S, RM, WIDE>;
+};
+
 // Columns per workgroup of the four-step passes: C * L values fill at most
 // 64 KiB of LDS, at least 4 columns for 32/64-byte contiguous runs.
 // EP > 0 sets the values per thread (the second four-step pass of the

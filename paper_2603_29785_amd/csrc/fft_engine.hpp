@@ -19,8 +19,12 @@
 // wave, which hold consecutive k, read consecutive entries; the other powers
 // are products of at most three of them. Four loads instead of fifteen per
 // radix-16 pass keep the twiddle traffic small next to the data streamed
-// through the caches. Direction S = -1 computes sum_n a_n e^{-2 pi i nk/L},
-// S = +1 the unnormalised inverse kernel e^{+2 pi i nk/L} (conjugated
+// through the caches: reading all fifteen where the table is a few KiB (stride
+// 16, from the L1 cache) saves 44 vector instructions and is slower all the
+// same (MI355X, 4096-value FP32 rows 490/575 us forward/inverse against
+// 477/541; 1024-value rows 128/161 against 112/141); six stored powers (1, 2,
+// 3, 4, 8, 12) are 2% slower than these four. Direction S = -1 computes
+// sum_n a_n e^{-2 pi i nk/L}, S = +1 the unnormalised inverse kernel e^{+2 pi i nk/L} (conjugated
 // twiddles).
 // Arithmetic: twiddles and rotations are applied inside the butterflies' fused
 // multiply-adds and LDS offsets are one address plus constants; against
@@ -295,16 +299,6 @@ constexpr int lds_size(int l) { return l + l / 32 + 1; }
 // lds_pad(i + c) for a c that shares no bit with i: lds_pad(i) plus a constant
 constexpr int lds_step(int c) { return c + (c >> 5); }
 
-// Twiddle table layouts: TW_POW stores the base powers w^1, w^2, w^4, w^8 of
-// each pass and forms the others by products (little table traffic, for
-// kernels that stream their data); TW_FULL stores every w^r, r in [1, R)
-// (no products, for kernels whose vector ALU is the limit); TW_MIXED stores
-// every power for passes of stride at most kFullStride (a table of a few KiB
-// that stays in the L1 cache) and base powers for the longer strides.
-enum TwiddleMode { TW_POW = 0, TW_FULL = 1, TW_MIXED = 2 };
-constexpr int kFullStride = 16;
-constexpr bool tw_full_pass(int mode, int ns) { return mode == TW_FULL || (mode == TW_MIXED && ns <= kFullStride); }
-
 // LDS a transform of length L needs: the padded exchange region, or half of
 // it when the whole one would not fit the 160 KiB of a workgroup (the
 // exchanges then go in two rounds, one per half of the destination indices).
@@ -317,15 +311,18 @@ constexpr int fft_lds_elems() {
   return fft_split<T, L>() ? lds_size(L / 2) : lds_size(L);
 }
 
-template <typename T, int L, int E, int S, int TW = TW_POW>
+// RM: largest butterfly; E = 2 RM holds two groups. HALF: the exchanges in two
+// rounds over half the region although the whole would fit (so that more rows
+// are resident on a CU).
+template <typename T, int L, int E, int S, int RM = (E < 16 ? E : 16), bool HALF = false>
 struct BlockFft {
   using C = typename Complex<T>::type;
-  static_assert((L & (L - 1)) == 0 && (E & (E - 1)) == 0 && E <= L && E <= 32, "pow2 sizes");
+  static_assert((L & (L - 1)) == 0 && (E & (E - 1)) == 0 && E <= L && E <= 2 * RM, "pow2 sizes");
   static constexpr int TPR = L / E;
-  static constexpr int RMAX = E < 16 ? E : 16;   // butterflies of at most radix 16; E = 32 holds two groups
+  static constexpr int RMAX = RM;
   static constexpr int radix(int ns) { return (L / ns >= RMAX) ? RMAX : L / ns; }
-  static constexpr bool SPLIT = fft_split<T, L>();
-  static constexpr int WN = E > 16 ? 16 : E;     // twiddle registers: one group at a time when E > 16
+  static constexpr bool SPLIT = HALF || fft_split<T, L>();
+  static constexpr int WN = E > RMAX ? RMAX : E;   // twiddle registers: one group at a time when E > RMAX
   static constexpr int last_ns() {
     int ns = 1;
     while (ns * radix(ns) < L) ns *= radix(ns);
@@ -333,16 +330,13 @@ struct BlockFft {
   }
   static constexpr int R0 = radix(1);
   static constexpr int RL = radix(last_ns());
-  // number of stored powers of the radix-R pass of stride ns: w^(2^s) < R,
-  // or all w^r, r < R
-  static constexpr int slots(int r, int ns) {
-    return tw_full_pass(TW, ns) ? r - 1 : (r >= 16 ? 4 : r >= 8 ? 3 : r >= 4 ? 2 : r >= 2 ? 1 : 0);
-  }
+  // number of stored powers of a radix-r pass: w^(2^s) < r
+  static constexpr int slots(int r) { return r >= 16 ? 4 : r >= 8 ? 3 : r >= 4 ? 2 : r >= 2 ? 1 : 0; }
   // start of the twiddle block of the pass with stride ns
   static constexpr int tw_offset(int ns) {
     int off = 0, n = 1;
     while (n < ns) {
-      if (n > 1) off += slots(radix(n), n) * n;
+      if (n > 1) off += slots(radix(n)) * n;
       n *= radix(n);
     }
     return off;
@@ -373,28 +367,22 @@ struct BlockFft {
 #pragma unroll
     for (int q = q0; q < q1; ++q) {
       const uint32_t k = static_cast<uint32_t>((tl + q * TPR) & (NS - 1));
-      if constexpr (tw_full_pass(TW, NS)) {
+      C a[16];
 #pragma unroll
-        for (int r = 1; r < R; ++r)
-          w[(q - q0) * R + r] = bload<C>(tw, k * sizeof(C), (tw_offset(NS) + (r - 1) * NS) * sizeof(C));
-      } else {
-        C a[16];
-#pragma unroll
-        for (int sl = 0; sl < slots(R, NS); ++sl)
-          a[1 << sl] = bload<C>(tw, k * sizeof(C), (tw_offset(NS) + sl * NS) * sizeof(C));
-        if constexpr (R > 2) a[3] = c_mul(a[2], a[1]);
-        if constexpr (R > 4) {
-          a[5] = c_mul(a[4], a[1]);
-          a[6] = c_mul(a[4], a[2]);
-          a[7] = c_mul(a[4], a[3]);
-        }
-        if constexpr (R > 8) {
-#pragma unroll
-          for (int r = 9; r < 16; ++r) a[r] = c_mul(a[8], a[r - 8]);
-        }
-#pragma unroll
-        for (int r = 1; r < R; ++r) w[(q - q0) * R + r] = a[r];
+      for (int sl = 0; sl < slots(R); ++sl)
+        a[1 << sl] = bload<C>(tw, k * sizeof(C), (tw_offset(NS) + sl * NS) * sizeof(C));
+      if constexpr (R > 2) a[3] = c_mul(a[2], a[1]);
+      if constexpr (R > 4) {
+        a[5] = c_mul(a[4], a[1]);
+        a[6] = c_mul(a[4], a[2]);
+        a[7] = c_mul(a[4], a[3]);
       }
+      if constexpr (R > 8) {
+#pragma unroll
+        for (int r = 9; r < 16; ++r) a[r] = c_mul(a[8], a[r - 8]);
+      }
+#pragma unroll
+      for (int r = 1; r < R; ++r) w[(q - q0) * R + r] = a[r];
     }
   }
 

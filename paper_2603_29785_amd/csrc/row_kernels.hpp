@@ -140,7 +140,7 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_tile_rows(
     const typename Complex<T>::type* __restrict__ tw) {
   using C = typename Complex<T>::type;
   using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, -1, TW_MIXED>;
+  using F = BlockFft<T, L, Geo::E, -1>;
   __shared__ C lds[Geo::G * fft_lds_elems<T, L>()];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   const int seg = static_cast<int>(blockIdx.x) * Geo::G + g;
@@ -276,8 +276,8 @@ __device__ __forceinline__ void row_sum(T s, int tl, bool ok, T* __restrict__ ds
 // the gradient G with respect to the masked envelope Y' = g_k m Y; the kernel
 // reads Y (mY, same layout as the output) and stores dL/dY instead, and the
 // row's sum of m Re(conj(Y) G) goes to mpart[row] (the gain gradient's share).
-template <typename T, int L, bool ANALYTIC, bool STATS, bool MBWD = false>
-__global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_fwd_rows(
+template <typename T, int L, bool ANALYTIC, bool STATS, bool MBWD = false, bool WIDE = false>
+__global__ __launch_bounds__((RowsGeom<T, L, WIDE>::NT), (WIDE ? 4 : 1)) void k_fwd_rows(
     const typename Complex<T>::type* __restrict__ spec, typename Complex<T>::type* __restrict__ Y,
     const RowMeta* __restrict__ rows, const typename Complex<T>::type* __restrict__ roww,
     const T* __restrict__ tab, int R, int total, int half, int sum_len, int64_t spec_elems,
@@ -285,10 +285,10 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_fwd_rows(
     const typename Complex<T>::type* __restrict__ mY, const T* __restrict__ mgain, const T* __restrict__ mlam,
     T* __restrict__ mpart) {
   using C = typename Complex<T>::type;
-  using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, +1, TW_MIXED>;
+  using Geo = RowsGeom<T, L, WIDE>;
+  using F = typename Geo::template Fft<+1>;
   constexpr bool kWaveRow = Geo::TPR >= 64;   // every lane of a wave is on the same row
-  __shared__ C lds[Geo::G * fft_lds_elems<T, L>()];
+  __shared__ C lds[Geo::G * Geo::LDS];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   const int u = xcd_major_block(nblocks);
   int gr = u * Geo::G + g;
@@ -361,14 +361,15 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_fwd_rows(
   // lane of this wave has zeros in first-pass inputs 1..14 (or 2..13) the
   // first pass skips them (same results, fewer operations).
   int nz = 0;
-  if constexpr (kWaveRow && F::R0 == 16 && Geo::E == 16) {
+  if constexpr (kWaveRow && F::R0 == 16) {
     const int jlo = rm.lo - rm.s, jhi = rm.hi - rm.s;
     const int t0 = __builtin_amdgcn_readfirstlane(tl) & ~63;
-    constexpr int Q = L / 16;   // input i of lane tl sits at slot tl + i Q
-    auto zero = [&](int a, int b) { return t0 + a * Q > jhi && t0 + 63 + b * Q < L + jlo; };
+    // input r of group q of lane tl sits at slot tl + q TPR + r Q
+    constexpr int Q = L / 16, TOP = 63 + (Geo::E / 16 - 1) * Geo::TPR;
+    auto zero = [&](int a, int b) { return t0 + a * Q > jhi && t0 + TOP + b * Q < L + jlo; };
     nz = !centred ? 0 : (zero(1, 14) ? 2 : (zero(2, 13) ? 4 : 0));
   }
-  F::run(v, lds + g * fft_lds_elems<T, L>(), tl, F::twiddles(tw), nz);
+  F::run(v, lds + g * Geo::LDS, tl, F::twiddles(tw), nz);
   const int64_t r0 = int64_t(u) * Geo::G;
   const int64_t nrow = total - r0 < Geo::G ? total - r0 : Geo::G;
   const rsrc_t ry = make_rsrc(Y + r0 * L, static_cast<uint32_t>(nrow * L * sizeof(C)));
@@ -398,16 +399,16 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_fwd_rows(
 // the other slots' stores without a test.
 // MASK (a masked inverse): each loaded value y becomes g_k max(0, 1 -
 // lambda_k / |y|) y (the mask of the denoiser) before the transform.
-template <typename T, int L, bool MASK = false>
-__global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows(
+template <typename T, int L, bool MASK = false, bool WIDE = false>
+__global__ __launch_bounds__((RowsGeom<T, L, WIDE>::NT), (WIDE ? 4 : 1)) void k_inv_rows(
     const typename Complex<T>::type* __restrict__ Y, typename Complex<T>::type* __restrict__ Sbuf,
     const RowMeta* __restrict__ rows, const T* __restrict__ tab, int R, int total, int sum_len, int segs,
     const typename Complex<T>::type* __restrict__ tw, const T* __restrict__ mgain, const T* __restrict__ mlam) {
   using C = typename Complex<T>::type;
-  using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, -1, TW_MIXED>;
+  using Geo = RowsGeom<T, L, WIDE>;
+  using F = typename Geo::template Fft<-1>;
   constexpr bool kWaveRow = Geo::TPR >= 64;
-  __shared__ C lds[Geo::G * fft_lds_elems<T, L>()];
+  __shared__ C lds[Geo::G * Geo::LDS];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   const int64_t r0 = int64_t(blockIdx.x) * Geo::G;
   const int64_t nrow = total - r0 < Geo::G ? total - r0 : Geo::G;
@@ -440,8 +441,8 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows(
     unsigned bw = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(T));
     opaque(bs);
     opaque(bw);
-    // (rows of 32 values per thread load them after the transform: registers)
-    constexpr bool kEarly = Geo::E <= 16;
+    // (rows of two groups per thread load them after the transform: registers)
+    constexpr bool kEarly = !WIDE && Geo::E <= 16;
     T w[kEarly ? Geo::E : 1];
     if constexpr (kEarly) {
 #pragma unroll
@@ -451,7 +452,7 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows(
         w[i] = bload<T>(rt, bw + j * static_cast<unsigned>(sizeof(T)));
       }
     }
-    F::run(v, lds + g * fft_lds_elems<T, L>(), tl, F::twiddles(tw));
+    F::run(v, lds + g * Geo::LDS, tl, F::twiddles(tw));
     if (!centred) {
       // a row of a regularised window: slot entries taken modulo L (the
       // early weights above are not used)
@@ -473,7 +474,7 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows(
       bstore<C, kSStore>(rs, C{v[i].x * wi, v[i].y * wi}, bs + j * static_cast<unsigned>(sizeof(C)));
     }
   } else {
-    F::run(v, lds + g * fft_lds_elems<T, L>(), tl, F::twiddles(tw));
+    F::run(v, lds + g * Geo::LDS, tl, F::twiddles(tw));
     const int gr = static_cast<int>(r0) + g;
     if (gr >= total) return;
     const int seg = gr / R;
@@ -505,8 +506,8 @@ __device__ __forceinline__ void chirp_convolve(C (&v)[E], C* lds, int tl, const 
                                                const C* __restrict__ tw) {
   using Geo = RowGeom<T, L>;
   static_assert(Geo::E == E, "row geometry");
-  using F = BlockFft<T, L, Geo::E, -1, TW_POW>;
-  using Fi = BlockFft<T, L, Geo::E, +1, TW_POW>;
+  using F = BlockFft<T, L, Geo::E, -1>;
+  using Fi = BlockFft<T, L, Geo::E, +1>;
   F::run(v, lds, tl, F::twiddles(tw));
 #pragma unroll
   for (int i = 0; i < Geo::E; ++i) v[i] = c_mul(v[i], bhat[tl + F::out_off(i)]);
@@ -531,8 +532,8 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_fwd_rows_bs(
     const typename Complex<T>::type* __restrict__ bhat, const typename Complex<T>::type* __restrict__ tw) {
   using C = typename Complex<T>::type;
   using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, -1, TW_POW>;
-  using Fi = BlockFft<T, L, Geo::E, +1, TW_POW>;
+  using F = BlockFft<T, L, Geo::E, -1>;
+  using Fi = BlockFft<T, L, Geo::E, +1>;
   __shared__ C lds[Geo::G * lds_size(L)];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   const int gr = static_cast<int>(blockIdx.x) * Geo::G + g;
@@ -581,8 +582,8 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows_bs(
     const typename Complex<T>::type* __restrict__ tw) {
   using C = typename Complex<T>::type;
   using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, -1, TW_POW>;
-  using Fi = BlockFft<T, L, Geo::E, +1, TW_POW>;
+  using F = BlockFft<T, L, Geo::E, -1>;
+  using Fi = BlockFft<T, L, Geo::E, +1>;
   __shared__ C lds[Geo::G * lds_size(L)];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   const int gr = static_cast<int>(blockIdx.x) * Geo::G + g;
@@ -640,10 +641,12 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows_bs(
 // being hoisted out of the block loop (they would take 64 registers and spill).
 // Measured on MI355X, FP32, 62 rows of 24576-sample segments: forward + inverse
 // of 128 segments with N_out = 12289 (support 1537) 11.45 ms by length-32768
-// transforms through memory, 0.88 ms here (L = 4096, 4 or 5 blocks); forward of
+// transforms through memory, 0.77 ms here (L = 4096, 4 or 5 blocks); forward of
 // 1024 segments with N_out = 1028 (support 1027) 0.87 ms by one length-4096
-// convolution per row, 0.72 ms here (L = 2048, one block for rows of at most
-// 507 bins a side, else two).
+// convolution per row, 0.57 ms here (L = 2048, one block for rows of at most
+// 507 bins a side, else two). Rows whose convolution over all outputs is
+// shorter than one per wave (1024 values FP32, 512 FP64) keep that form: here
+// 8700 rows of 109 values, forward + inverse, took 69 us against 51.
 struct OsPlan {
   int M, JP, B;          // N_out, largest positive offset, block step
   int nmax;              // blocks of the table Bhat
@@ -661,66 +664,43 @@ constexpr int os_in_reg(int i) {
 template <typename T, int L>
 __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
     const typename Complex<T>::type* __restrict__ spec, typename Complex<T>::type* __restrict__ Y,
-    const RowMeta* __restrict__ rows, const T* __restrict__ tab, int R, int total, int half, OsPlan os,
+    const RowMeta* __restrict__ rows, const typename Complex<T>::type* __restrict__ tab, int R, int total, int half, OsPlan os,
     const typename Complex<T>::type* __restrict__ chirp, const typename Complex<T>::type* __restrict__ bhat,
     const typename Complex<T>::type* __restrict__ tw, int nblocks) {
   using C = typename Complex<T>::type;
   using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, -1, TW_MIXED>;
-  using Fi = BlockFft<T, L, Geo::E, +1, TW_MIXED>;
-  constexpr bool kWaveRow = Geo::TPR >= 64;
+  using F = BlockFft<T, L, Geo::E, -1>;
+  using Fi = BlockFft<T, L, Geo::E, +1>;
+  static_assert(Geo::TPR >= 64, "a wave holds one row");
   __shared__ C lds[Geo::G * lds_size(L)];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   C* reg = lds + g * lds_size(L);
   const int u = xcd_major_block(nblocks);
   int gr = u * Geo::G + g;
-  if constexpr (kWaveRow) gr = __builtin_amdgcn_readfirstlane(gr);
+  gr = __builtin_amdgcn_readfirstlane(gr);
   const bool ok = gr < total;
   const int seg = ok ? gr / R : 0;
   const RowMeta rm = rows[ok ? gr - seg * R : 0];
   const int len = ok ? rm.hi - rm.lo + 1 : 0;
   const int jlo = rm.lo - rm.s, jhi = rm.hi - rm.s;
   const int nb = __builtin_amdgcn_readfirstlane(os.blocks[(u * Geo::G) % R]);
+  if (static_cast<int>(blockIdx.y) >= nb) return;
   const rsrc_t rc = make_rsrc(chirp, static_cast<uint32_t>(os.M * sizeof(C)));
   C v[Geo::E];
   {
     // kept bins c = s + j at slot j mod L (j the signed slot), times the table
-    // and the chirp; slots outside the support read 0
+    // (window and chirp); slots outside the support read 0
     const C* Z = spec + int64_t(seg) * half;
     const C z0 = Z[0];   // (X[0], X[N/2])
-    const int db = tl - jlo;   // d = c - lo of the slot with offset 0
-    rsrc_t rz, rt;
-    if constexpr (kWaveRow) {
-      rz = make_rsrc(Z + rm.lo, static_cast<uint32_t>((ok && rm.hi == half ? len - 1 : len) * sizeof(C)));
-      rt = make_rsrc(tab + rm.off, static_cast<uint32_t>(len * sizeof(T)));
-    }
-    unsigned bx = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(C));
-    unsigned bw = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(T));
-    unsigned bp = static_cast<unsigned>(tl) * static_cast<unsigned>(sizeof(C)), bn = 0u - bp;   // chirp[|j|]
+    const rsrc_t rz = make_rsrc(Z + rm.lo, static_cast<uint32_t>((ok && rm.hi == half ? len - 1 : len) * sizeof(C)));
+    const rsrc_t rt = make_rsrc(tab + rm.off, static_cast<uint32_t>(len * sizeof(C)));
+    unsigned bx = static_cast<unsigned>(tl - jlo) * static_cast<unsigned>(sizeof(C));   // d = c - lo of offset 0
     opaque(bx);
-    opaque(bw);
-    opaque(bp);
-    opaque(bn);
 #pragma unroll
     for (int i = 0; i < Geo::E; ++i) {
       const int off = F::in_off(i);
-      const bool pos = off < L / 2;
-      const unsigned j = static_cast<unsigned>(pos ? off : off - L);
-      C x{0, 0};
-      T w = 0;
-      if constexpr (kWaveRow) {
-        x = bload<C>(rz, bx + j * static_cast<unsigned>(sizeof(C)));
-        w = bload<T>(rt, bw + j * static_cast<unsigned>(sizeof(T)));
-      } else {
-        const int d = db + static_cast<int>(j);
-        if (static_cast<unsigned>(d) < static_cast<unsigned>(len)) {
-          x = Z[rm.lo + d == half ? 0 : rm.lo + d];
-          w = tab[rm.off + d];
-        }
-      }
-      const C a = bload<C>(rc, pos ? bp + static_cast<unsigned>(off * int(sizeof(C)))
-                                   : bn + static_cast<unsigned>((L - off) * int(sizeof(C))));
-      v[i] = c_mul(C{x.x * w, x.y * w}, a);
+      const unsigned j = static_cast<unsigned>(off < L / 2 ? off : off - L) * static_cast<unsigned>(sizeof(C));
+      v[i] = c_mul(bload<C>(rz, bx + j), bload<C>(rt, bx + j));
     }
     if (rm.lo == 0 || rm.hi == half) {
 #pragma unroll
@@ -729,15 +709,15 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
         const int c = rm.s + tl + (off < L / 2 ? off : off - L);
         const bool dc = c == 0 && rm.lo == 0, ny = c == half && rm.hi == half;
         if (ok && (dc || ny)) {
-          const T w = (dc ? z0.x : z0.y) * tab[rm.off + (c - rm.lo)];
-          const C a = chirp[c < rm.s ? rm.s - c : c - rm.s];
-          v[i] = C{w * a.x, w * a.y};
+          const C w = tab[rm.off + (c - rm.lo)];
+          const T x = dc ? z0.x : z0.y;
+          v[i] = C{x * w.x, x * w.y};
         }
       }
     }
   }
   int nz = 0;
-  if constexpr (kWaveRow && F::R0 == 16 && Geo::E == 16) {
+  if constexpr (F::R0 == 16 && Geo::E == 16) {
     const int t0 = __builtin_amdgcn_readfirstlane(tl) & ~63;
     constexpr int Q = L / 16;   // input i of lane tl sits at slot tl + i Q
     auto zero = [&](int a, int b) { return t0 + a * Q > jhi && t0 + 63 + b * Q < L + jlo; };
@@ -746,8 +726,11 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
   F::run(v, reg, tl, F::twiddles(tw), nz);
   C* yrow = Y + int64_t(ok ? gr : 0) * os.M;
   const rsrc_t rb = make_rsrc(bhat, static_cast<uint32_t>(os.nmax * L * int(sizeof(C))));
-  int done = 0;   // outputs already stored
-  for (int b = 0; b < nb; ++b) {
+  // all blocks of the rows, or (few rows: the input transform repeated instead
+  // of a workgroup's blocks in series) the one of blockIdx.y
+  const int b0 = gridDim.y > 1 ? static_cast<int>(blockIdx.y) : 0, b1 = gridDim.y > 1 ? b0 + 1 : nb;
+  int done = b0 == 0 ? 0 : (b0 - 1) * os.B - os.JP + L + jlo;   // outputs stored by the blocks before
+  for (int b = b0; b < b1; ++b) {
     const int tb = opaque_copy(tl);   // keeps the transform's table loads in the loop (registers)
     C z[Geo::E];
 #pragma unroll
@@ -765,18 +748,11 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
       unsigned bs = static_cast<unsigned>(V + tl - done) * static_cast<unsigned>(sizeof(C));
       opaque(bc);
       opaque(bs);
-      rsrc_t ry;
-      if constexpr (kWaveRow) ry = make_rsrc(yrow + done, static_cast<uint32_t>((end - done) * sizeof(C)));
+      const rsrc_t ry = make_rsrc(yrow + done, static_cast<uint32_t>((end - done) * sizeof(C)));
 #pragma unroll
       for (int i = 0; i < Geo::E; ++i) {
         const unsigned o = static_cast<unsigned>(Fi::out_off(i)) * static_cast<unsigned>(sizeof(C));
-        const C y = c_mul(z[i], bload<C>(rc, bc + o));
-        if constexpr (kWaveRow) {
-          bstore<C, kYStore>(ry, y, bs + o);
-        } else {
-          const int m = V + tl + Fi::out_off(i);
-          if (m >= done && m < end) yrow[m] = y;
-        }
+        bstore<C, kYStore>(ry, c_mul(z[i], bload<C>(rc, bc + o)), bs + o);
       }
       done = end;
     }
@@ -786,20 +762,20 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
 template <typename T, int L>
 __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_inv_rows_os(
     const typename Complex<T>::type* __restrict__ Y, typename Complex<T>::type* __restrict__ Sbuf,
-    const RowMeta* __restrict__ rows, const T* __restrict__ tab, int R, int total, int sum_len, OsPlan os,
+    const RowMeta* __restrict__ rows, const typename Complex<T>::type* __restrict__ tab, int R, int total, int sum_len, OsPlan os,
     const typename Complex<T>::type* __restrict__ chirp, const typename Complex<T>::type* __restrict__ bhat,
     const typename Complex<T>::type* __restrict__ tw) {
   using C = typename Complex<T>::type;
   using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, -1, TW_MIXED>;
-  using Fi = BlockFft<T, L, Geo::E, +1, TW_MIXED>;
-  constexpr bool kWaveRow = Geo::TPR >= 64;
+  using F = BlockFft<T, L, Geo::E, -1>;
+  using Fi = BlockFft<T, L, Geo::E, +1>;
+  static_assert(Geo::TPR >= 64, "a wave holds one row");
   __shared__ C lds[Geo::G * lds_size(L)];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   C* reg = lds + g * lds_size(L);
   const int u = static_cast<int>(blockIdx.x);
   int gr = u * Geo::G + g;
-  if constexpr (kWaveRow) gr = __builtin_amdgcn_readfirstlane(gr);
+  gr = __builtin_amdgcn_readfirstlane(gr);
   const bool ok = gr < total;
   const int seg = ok ? gr / R : 0;
   const RowMeta rm = rows[ok ? gr - seg * R : 0];
@@ -821,20 +797,12 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_inv_rows_os(
     unsigned by = static_cast<unsigned>(V + tl - done) * static_cast<unsigned>(sizeof(C));
     opaque(bc);
     opaque(by);
-    rsrc_t ry;
-    if constexpr (kWaveRow) ry = make_rsrc(yrow + done, static_cast<uint32_t>((end - done) * sizeof(C)));
+    const rsrc_t ry = make_rsrc(yrow + done, static_cast<uint32_t>((end - done) * sizeof(C)));
     C v[Geo::E];
 #pragma unroll
     for (int i = 0; i < Geo::E; ++i) {
       const unsigned o = static_cast<unsigned>(F::in_off(i)) * static_cast<unsigned>(sizeof(C));
-      C y{0, 0};
-      if constexpr (kWaveRow) {
-        y = bload<C>(ry, by + o);
-      } else {
-        const int m = V + tl + F::in_off(i);
-        if (m >= done && m < end) y = yrow[m];
-      }
-      v[i] = c_mul(y, c_conj(bload<C>(rc, bc + o)));
+      v[i] = c_mul(bload<C>(ry, by + o), c_conj(bload<C>(rc, bc + o)));
     }
     F::run(v, reg, opaque_copy(tl), F::twiddles(tw));   // (table loads stay in the loop: registers)
     __builtin_amdgcn_sched_barrier(0);
@@ -854,39 +822,17 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_inv_rows_os(
   }
   Fi::run(z, reg, tl, Fi::twiddles(tw));
   if (!ok) return;
-  // slot j mod L holds the kept entry d = j - jlo
-  const int db = tl - jlo;
-  C* srow = Sbuf + int64_t(seg) * sum_len + rm.off;
-  rsrc_t rs, rt;
-  if constexpr (kWaveRow) {
-    rs = make_rsrc(srow, static_cast<uint32_t>(len * sizeof(C)));
-    rt = make_rsrc(tab + rm.off, static_cast<uint32_t>(len * sizeof(T)));
-  }
-  unsigned bs = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(C));
-  unsigned bw = static_cast<unsigned>(db) * static_cast<unsigned>(sizeof(T));
-  unsigned bp = static_cast<unsigned>(tl) * static_cast<unsigned>(sizeof(C)), bn = 0u - bp;
+  // slot j mod L holds the kept entry d = j - jlo; the table holds its
+  // conjugate chirp too
+  const rsrc_t rs = make_rsrc(Sbuf + int64_t(seg) * sum_len + rm.off, static_cast<uint32_t>(len * sizeof(C)));
+  const rsrc_t rt = make_rsrc(tab + rm.off, static_cast<uint32_t>(len * sizeof(C)));
+  unsigned bs = static_cast<unsigned>(tl - jlo) * static_cast<unsigned>(sizeof(C));
   opaque(bs);
-  opaque(bw);
-  opaque(bp);
-  opaque(bn);
 #pragma unroll
   for (int i = 0; i < Geo::E; ++i) {
     const int off = Fi::out_off(i);
-    const bool pos = off < L / 2;
-    const unsigned j = static_cast<unsigned>(pos ? off : off - L);
-    const C a = bload<C>(rc, pos ? bp + static_cast<unsigned>(off * int(sizeof(C)))
-                                 : bn + static_cast<unsigned>((L - off) * int(sizeof(C))));
-    const C x = c_mul(z[i], c_conj(a));
-    if constexpr (kWaveRow) {
-      const T w = bload<T>(rt, bw + j * static_cast<unsigned>(sizeof(T)));
-      bstore<C, kSStore>(rs, C{x.x * w, x.y * w}, bs + j * static_cast<unsigned>(sizeof(C)));
-    } else {
-      const int d = db + static_cast<int>(j);
-      if (static_cast<unsigned>(d) < static_cast<unsigned>(len)) {
-        const T w = tab[rm.off + d];
-        srow[d] = C{x.x * w, x.y * w};
-      }
-    }
+    const unsigned j = static_cast<unsigned>(off < L / 2 ? off : off - L) * static_cast<unsigned>(sizeof(C));
+    bstore<C>(rs, c_mul(z[i], bload<C>(rt, bs + j)), bs + j);
   }
 }
 

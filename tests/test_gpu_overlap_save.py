@@ -18,6 +18,7 @@ CAP = {"cover": o.CAP_COVER, "paper": o.CAP_PAPER, "none": o.CAP_NONE}
 CASES = {
     "few_values_per_row": (256.0, 64, 4.0, 16.0, 100.0, 5, 9, "none", 3, False),
     "several_rows_per_workgroup": (1024.0, 1024, 4.0, 8.0, 400.0, 7, 117, "cover", 3, True),
+    "ragged_workgroups": (1024.0, 4096, 6.0, 30.0, 100.0, 7, 333, "cover", 3, False),
     "support_from_dc_to_nyquist": (1024.0, 1024, 0.5, 8.0, 512.0, 9, 1030, "none", 2, True),
     "narrowest_envelope": (4096.0, 24576, 8.0, 10.0, 2048.0, 62, 1537, "cover", 2, True),
     "one_and_two_blocks": (4096.0, 24576, 8.0, 10.0, 2048.0, 62, 1028, "paper", 2, False),
