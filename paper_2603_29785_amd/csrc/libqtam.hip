@@ -33,6 +33,7 @@
 #include <mutex>
 #include <string>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "mask_kernels.hpp"
@@ -186,7 +187,7 @@ namespace {
 // ---------------------------------------------------------------------------
 // In-place forward DFT (e^{-2 pi i k n / L}) of a power-of-two length in
 // FP64 on the host: bit reversal, then butterflies with every twiddle from
-// its own angle.
+// its own angle (those of the last stage, which hold the others).
 void host_fft(std::vector<std::complex<double>>& a) {
   const int64_t n = static_cast<int64_t>(a.size());
   for (int64_t i = 1, j = 0; i < n; ++i) {
@@ -195,11 +196,13 @@ void host_fft(std::vector<std::complex<double>>& a) {
     j ^= bit;
     if (i < j) std::swap(a[i], a[j]);
   }
+  std::vector<std::complex<double>> w(n / 2);
+  for (int64_t k = 0; k < n / 2; ++k)
+    w[k] = std::polar(1.0, -2.0 * M_PI * static_cast<double>(k) / static_cast<double>(n));
   for (int64_t len = 2; len <= n; len <<= 1)
     for (int64_t i = 0; i < n; i += len)
       for (int64_t k = 0; k < len / 2; ++k) {
-        const std::complex<double> w = std::polar(1.0, -2.0 * M_PI * static_cast<double>(k) / static_cast<double>(len));
-        const std::complex<double> u = a[i + k], t = a[i + k + len / 2] * w;
+        const std::complex<double> u = a[i + k], t = a[i + k + len / 2] * w[k * (n / len)];
         a[i + k] = u + t;
         a[i + k + len / 2] = u - t;
       }
@@ -303,6 +306,11 @@ qtam_status upload(qtam_plan_s* pl) {
   auto chirp = [&](int64_t v) {   // e^{+pi i v^2 / N_out}, v^2 reduced mod 2 N_out exactly
     return std::polar(1.0, M_PI * static_cast<double>((v * v) % (2 * int64_t(hp.n_out))) / static_cast<double>(hp.n_out));
   };
+  std::vector<std::complex<double>> row_chirp;   // by |c - centre|
+  if (pl->bs_os) {
+    row_chirp.resize(hp.max_len / 2 + 1);
+    for (size_t j = 0; j < row_chirp.size(); ++j) row_chirp[j] = chirp(static_cast<int64_t>(j));
+  }
   for (int i = 0; i < 6; ++i) {
     std::vector<T> v;
     if (pl->bs_os) {   // overlap-save rows: the entries times their chirp (conjugate in the inverse direction)
@@ -311,7 +319,7 @@ qtam_status upload(qtam_plan_s* pl) {
       for (int k = 0; k < hp.rows; ++k)
         for (int64_t c = hp.lo[k]; c <= hp.hi[k]; ++c) {
           const int64_t e = hp.offset[k] + (c - hp.lo[k]);
-          const std::complex<double> a = (*src[i])[e] * chirp(c - hp.centre[k]);
+          const std::complex<double> a = (*src[i])[e] * row_chirp[c > hp.centre[k] ? c - hp.centre[k] : hp.centre[k] - c];
           v[2 * e] = static_cast<T>(a.real());
           v[2 * e + 1] = static_cast<T>(sign * a.imag());
         }
@@ -1202,10 +1210,21 @@ bool dense_transform(qtam_plan_s* pl, const void* pack, void* dense, int64_t cou
 #define X(LG)                                                                                           \
   case LG:                                                                                              \
     if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Single32 : kMaxLog2Single64)) {                     \
-      using Geo = RowGeom<T, (1 << LG)>;                                                                \
-      hipLaunchKernelGGL((k_dense_rows<T, (1 << LG), R>), dim3(unsigned((count + Geo::G - 1) / Geo::G * R)), \
-                         dim3(Geo::NT), 0, st, static_cast<const C*>(pack), static_cast<C*>(dense), pl->d_rows, \
-                         hp.rows, count, int64_t(hp.sum_len), static_cast<const C*>(pl->d_tw_dense), tw2_of<T>(pl)); \
+      auto launch = [&](auto wide) {                                                                    \
+        using Geo = RowsGeom<T, (1 << LG), decltype(wide)::value>;                                      \
+        hipLaunchKernelGGL((k_dense_rows<T, (1 << LG), R, decltype(wide)::value>),                      \
+                           dim3(unsigned((count + Geo::G - 1) / Geo::G * R)), dim3(Geo::NT), 0, st,     \
+                           static_cast<const C*>(pack), static_cast<C*>(dense), pl->d_rows, hp.rows, count, \
+                           int64_t(hp.sum_len), static_cast<const C*>(pl->d_tw_dense), tw2_of<T>(pl));  \
+      };                                                                                                \
+      constexpr int64_t row_bytes = (int64_t(1) << LG) * 2 * sizeof(T);                                 \
+      if constexpr (R == 1 && wide_rows<T, (1 << LG)>()) {                                              \
+        if (count * row_bytes >= wide_from_bytes(row_bytes)) {                                      \
+          launch(std::true_type{});                                                                     \
+          return true;                                                                                  \
+        }                                                                                               \
+      }                                                                                                 \
+      launch(std::false_type{});                                                                        \
       return true;                                                                                      \
     }                                                                                                   \
     return false;

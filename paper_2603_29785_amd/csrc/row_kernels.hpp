@@ -55,16 +55,18 @@ __device__ __forceinline__ void dense_values(typename Complex<T>::type (&v)[E], 
 // write of the tiles. Measured on MI355X, FP32, 16 x 24576 samples, 62 rows
 // (R = 3, 195 MB of tiles), forward + dense: 306 us with placing, radix pass,
 // transforms and permutation as passes of their own, 123 us with this kernel;
-// 16 x 16384 samples (R = 1) 126 to 81 us.
-template <typename T, int L, int R>
-__global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_dense_rows(
+// 16 x 16384 samples (R = 1) 126 to 78 us, and to 68 us in the two-group form
+// (wide_from_bytes); with R = 3 that form has more rows between the parts of a
+// line and is slower (162 us), so siblings keep one group.
+template <typename T, int L, int R, bool WIDE = false>
+__global__ __launch_bounds__((RowsGeom<T, L, WIDE>::NT), (WIDE ? 4 : 1)) void k_dense_rows(
     const typename Complex<T>::type* __restrict__ Sbuf, typename Complex<T>::type* __restrict__ D,
     const RowMeta* __restrict__ rows, int nrows, int64_t count, int64_t sum_len,
     const typename Complex<T>::type* __restrict__ tw, Twiddle2<typename Complex<T>::type> tw2) {
   using C = typename Complex<T>::type;
-  using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, +1>;
-  __shared__ C lds[Geo::G * lds_size(L)];
+  using Geo = RowsGeom<T, L, WIDE>;
+  using F = typename Geo::template Fft<+1>;
+  __shared__ C lds[Geo::G * Geo::LDS];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   int64_t u = blockIdx.x;
   int n1 = 0;
@@ -90,7 +92,7 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_dense_rows(
       }
     }
   }
-  F::run(v, lds + g * lds_size(L), tl, F::twiddles(tw));
+  F::run(v, lds + g * Geo::LDS, tl, F::twiddles(tw));
   if (!ok) return;
   C* dst = D + int64_t(gr) * (R * L) + n1 + R * tl;
 #pragma unroll

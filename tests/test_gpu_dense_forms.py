@@ -34,3 +34,21 @@ def test_dense_forms(case, precision):
     T = np.fft.ifft(Z)
     err = np.linalg.norm((D - T).reshape(B, -1), axis=1) / np.linalg.norm(T.reshape(B, -1), axis=1)
     assert err.max() <= TOL[precision], err
+
+
+@pytest.mark.parametrize("precision,n,rows,B", [("fp32", 24576, 62, 7), ("fp32", 16384, 100, 8), ("fp64", 24576, 40, 3),
+                                                ("fp64", 5 * 4096, 64, 3), ("fp32", 4096, 200, 45)])
+def test_dense_many_rows_same_bits(precision, n, rows, B):
+    """A batch whose tiles take the two-group form gives each segment the bits
+    it has alone."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_29785_amd as qt
+    print("case", precision, n, rows, B, flush=True)
+    p = qt.Plan(4096.0, n, 8.0, 20.0, 2000.0, rows, precision=precision)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((B, n), generator=gen, device="cuda", dtype=torch.float64 if precision == "fp64" else torch.float32)
+    D = p.dense(p.forward(x))
+    for i in (0, B - 1):
+        assert torch.equal(p.dense(p.forward(x[i:i + 1])), D[i:i + 1])
