@@ -91,7 +91,7 @@ struct RowsGeom {
   static constexpr int G = TPR >= 256 ? 1 : 256 / TPR;
   static constexpr int NT = G * TPR;
   static constexpr int LDS = WIDE ? lds_size(L / 2) : fft_lds_elems<T, L>();
-  template <int S> using Fft = BlockFft<T, L, E, S, RM, WIDE>;
+  template <int S, int TW = TW_MIXED> using Fft = BlockFft<T, L, E, S, TW, RM, WIDE>;
 };
 
 // Columns per workgroup of the four-step passes: C * L values fill at most

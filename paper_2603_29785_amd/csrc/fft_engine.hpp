@@ -13,19 +13,20 @@
 //   before the first pass: v[q*R0 + r] = a[tl + q*TPR + r*(L/R0)]
 //   after the last pass:   v[q*RL + r] = A[tl + q*TPR + r*(L/RL)]
 // Twiddles: every pass after the first (stride NS, radix R) needs
-// w^r, w = exp(-2 pi i k / (NS R)), r in [1, R), for its k = j mod NS. A
-// per-pass table built on the host in FP64 holds only the base powers
-// w^1, w^2, w^4, w^8 (those below R) in blocks [s*NS + k], so the threads of a
-// wave, which hold consecutive k, read consecutive entries; the other powers
-// are products of at most three of them. Four loads instead of fifteen per
-// radix-16 pass keep the twiddle traffic small next to the data streamed
-// through the caches: reading all fifteen where the table is a few KiB (stride
-// 16, from the L1 cache) saves 44 vector instructions and is slower all the
-// same (MI355X, 4096-value FP32 rows 490/575 us forward/inverse against
-// 477/541; 1024-value rows 128/161 against 112/141); six stored powers (1, 2,
-// 3, 4, 8, 12) are 2% slower than these four. Direction S = -1 computes
-// sum_n a_n e^{-2 pi i nk/L}, S = +1 the unnormalised inverse kernel e^{+2 pi i nk/L} (conjugated
-// twiddles).
+// w^r, w = exp(-2 pi i k / (NS R)), r in [1, R), for its k = j mod NS, from a
+// per-pass table built on the host in FP64, in blocks [s*NS + k], so the
+// threads of a wave, which hold consecutive k, read consecutive entries.
+// TW_POW stores only the base powers w^1, w^2, w^4, w^8 (those below R); the
+// other powers are products of at most three of them: four loads instead of
+// fifteen per radix-16 pass keep the twiddle traffic small next to the data
+// streamed through the caches, where the table is long. TW_MIXED (the envelope
+// rows) stores every power for passes of stride at most kFullStride, a table
+// of a few KiB that stays in the L1 cache: each twiddle is then rounded once.
+// With products in that pass too a row's FP32 error is 5 to 7% larger and its
+// systematic part, a scale below 1, 34 to 52% (rel-L2 of 512 / 2048 / 4096
+// points 1.12e-7 / 1.26e-7 / 1.35e-7 against 1.04e-7 / 1.19e-7 / 1.29e-7).
+// Direction S = -1 computes sum_n a_n e^{-2 pi i nk/L}, S = +1 the
+// unnormalised inverse kernel e^{+2 pi i nk/L} (conjugated twiddles).
 // Arithmetic: twiddles and rotations are applied inside the butterflies' fused
 // multiply-adds and LDS offsets are one address plus constants; against
 // rounding each product first and one address per element this takes 733
@@ -299,6 +300,11 @@ constexpr int lds_size(int l) { return l + l / 32 + 1; }
 // lds_pad(i + c) for a c that shares no bit with i: lds_pad(i) plus a constant
 constexpr int lds_step(int c) { return c + (c >> 5); }
 
+// Twiddle tables of the passes (see above).
+enum TwiddleMode { TW_POW = 0, TW_MIXED = 1 };
+constexpr int kFullStride = 16;
+constexpr bool tw_full_pass(int mode, int ns) { return mode == TW_MIXED && ns <= kFullStride; }
+
 // LDS a transform of length L needs: the padded exchange region, or half of
 // it when the whole one would not fit the 160 KiB of a workgroup (the
 // exchanges then go in two rounds, one per half of the destination indices).
@@ -314,7 +320,7 @@ constexpr int fft_lds_elems() {
 // RM: largest butterfly; E = 2 RM holds two groups. HALF: the exchanges in two
 // rounds over half the region although the whole would fit (so that more rows
 // are resident on a CU).
-template <typename T, int L, int E, int S, int RM = (E < 16 ? E : 16), bool HALF = false>
+template <typename T, int L, int E, int S, int TW = TW_POW, int RM = (E < 16 ? E : 16), bool HALF = false>
 struct BlockFft {
   using C = typename Complex<T>::type;
   static_assert((L & (L - 1)) == 0 && (E & (E - 1)) == 0 && E <= L && E <= 2 * RM, "pow2 sizes");
@@ -330,13 +336,16 @@ struct BlockFft {
   }
   static constexpr int R0 = radix(1);
   static constexpr int RL = radix(last_ns());
-  // number of stored powers of a radix-r pass: w^(2^s) < r
-  static constexpr int slots(int r) { return r >= 16 ? 4 : r >= 8 ? 3 : r >= 4 ? 2 : r >= 2 ? 1 : 0; }
+  // number of stored powers of the radix-r pass of stride ns: w^(2^s) < r, or
+  // all w^s, s < r
+  static constexpr int slots(int r, int ns) {
+    return tw_full_pass(TW, ns) ? r - 1 : r >= 16 ? 4 : r >= 8 ? 3 : r >= 4 ? 2 : r >= 2 ? 1 : 0;
+  }
   // start of the twiddle block of the pass with stride ns
   static constexpr int tw_offset(int ns) {
     int off = 0, n = 1;
     while (n < ns) {
-      if (n > 1) off += slots(radix(n)) * n;
+      if (n > 1) off += slots(radix(n), n) * n;
       n *= radix(n);
     }
     return off;
@@ -358,7 +367,7 @@ struct BlockFft {
   }
 
   // Twiddles of the pass with stride NS for this thread: w[q*R + r], r >= 1,
-  // from the base powers w^1, w^2, w^4, w^8 (groups q0 .. q1-1, stored from
+  // read, or formed from the base powers w^1, w^2, w^4, w^8 (groups q0 .. q1-1, stored from
   // w[0] on when only one group is held at a time).
   template <int NS>
   __device__ static __forceinline__ void load_twiddles(C (&w)[WN], int tl, rsrc_t tw, int q0 = 0,
@@ -367,22 +376,28 @@ struct BlockFft {
 #pragma unroll
     for (int q = q0; q < q1; ++q) {
       const uint32_t k = static_cast<uint32_t>((tl + q * TPR) & (NS - 1));
-      C a[16];
+      if constexpr (tw_full_pass(TW, NS)) {
 #pragma unroll
-      for (int sl = 0; sl < slots(R); ++sl)
-        a[1 << sl] = bload<C>(tw, k * sizeof(C), (tw_offset(NS) + sl * NS) * sizeof(C));
-      if constexpr (R > 2) a[3] = c_mul(a[2], a[1]);
-      if constexpr (R > 4) {
-        a[5] = c_mul(a[4], a[1]);
-        a[6] = c_mul(a[4], a[2]);
-        a[7] = c_mul(a[4], a[3]);
+        for (int r = 1; r < R; ++r)
+          w[(q - q0) * R + r] = bload<C>(tw, k * sizeof(C), (tw_offset(NS) + (r - 1) * NS) * sizeof(C));
+      } else {
+        C a[16];
+#pragma unroll
+        for (int sl = 0; sl < slots(R, NS); ++sl)
+          a[1 << sl] = bload<C>(tw, k * sizeof(C), (tw_offset(NS) + sl * NS) * sizeof(C));
+        if constexpr (R > 2) a[3] = c_mul(a[2], a[1]);
+        if constexpr (R > 4) {
+          a[5] = c_mul(a[4], a[1]);
+          a[6] = c_mul(a[4], a[2]);
+          a[7] = c_mul(a[4], a[3]);
+        }
+        if constexpr (R > 8) {
+#pragma unroll
+          for (int r = 9; r < 16; ++r) a[r] = c_mul(a[8], a[r - 8]);
+        }
+#pragma unroll
+        for (int r = 1; r < R; ++r) w[(q - q0) * R + r] = a[r];
       }
-      if constexpr (R > 8) {
-#pragma unroll
-        for (int r = 9; r < 16; ++r) a[r] = c_mul(a[8], a[r - 8]);
-      }
-#pragma unroll
-      for (int r = 1; r < R; ++r) w[(q - q0) * R + r] = a[r];
     }
   }
 

@@ -126,7 +126,7 @@ struct qtam_plan_s {
   int* d_one_start = nullptr;   // overlap-add lists of a single row over all bins
   OlaRow* d_one_rows = nullptr;
   void* d_tab[6] = {};
-  void* d_tw_out = nullptr;     // N_out (the row kernels)
+  void* d_tw_out = nullptr;     // N_out, TW_MIXED layout (the row kernels)
   void* d_tw_half = nullptr;    // M2 (single pass) or nullptr
   void* d_tw_n1 = nullptr;      // N1 (four-step, second pass length)
   void* d_tw_n2 = nullptr;      // N2 (four-step, first pass length)
@@ -223,16 +223,18 @@ void twiddles_strided(std::vector<T>& out, int64_t count, int64_t step, int64_t 
 // Per-pass twiddle table of the block FFT of length L with e values per
 // thread, in the order the engine reads it (see BlockFft::tw_offset): for
 // each pass with stride ns > 1 and radix R, exp(-2 pi i r k / (ns R)),
-// k in [0, ns), for r = 1, 2, 4, 8 (< R).
+// k in [0, ns), for r = 1, 2, 4, 8 (< R) or for every r in [1, R), as
+// tw_full_pass(mode, ns) says.
 template <typename T>
-void stockham_twiddles(std::vector<T>& out, int64_t L, int64_t e) {
+void stockham_twiddles(std::vector<T>& out, int64_t L, int64_t e, int mode = TW_POW) {
   out.clear();
   const int64_t rmax = std::min<int64_t>(e, 16);   // butterflies of at most radix 16
   auto radix = [&](int64_t ns) { return (L / ns >= rmax) ? rmax : L / ns; };
   for (int64_t ns = 1; ns < L; ns *= radix(ns)) {
     const int64_t R = radix(ns);
     if (ns == 1) continue;
-    for (int64_t r = 1; r < R; r *= 2)
+    const bool full = tw_full_pass(mode, static_cast<int>(ns));
+    for (int64_t r = 1; r < R; r = full ? r + 1 : 2 * r)
       for (int64_t k = 0; k < ns; ++k) {
         const double a = -2.0 * M_PI * static_cast<double>(r * k) / static_cast<double>(ns * R);
         out.push_back(static_cast<T>(std::cos(a)));
@@ -339,7 +341,7 @@ qtam_status upload(qtam_plan_s* pl) {
   const bool f64 = sizeof(T) == 8;
   std::vector<T> tw;
   if (pl->bluestein) tw.assign(2, T(0));
-  else stockham_twiddles(tw, hp.n_out, engine_e(hp.n_out, f64));
+  else stockham_twiddles(tw, hp.n_out, engine_e(hp.n_out, f64), TW_MIXED);
   const size_t o_out = blob.add(tw.data(), tw.size() * sizeof(T));
   size_t o_half = 0, o_n1 = 0, o_n2 = 0;
   if (!pl->four_step) {

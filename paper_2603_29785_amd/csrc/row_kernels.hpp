@@ -65,7 +65,7 @@ __global__ __launch_bounds__((RowsGeom<T, L, WIDE>::NT), (WIDE ? 4 : 1)) void k_
     const typename Complex<T>::type* __restrict__ tw, Twiddle2<typename Complex<T>::type> tw2) {
   using C = typename Complex<T>::type;
   using Geo = RowsGeom<T, L, WIDE>;
-  using F = typename Geo::template Fft<+1>;
+  using F = typename Geo::template Fft<+1, TW_POW>;
   __shared__ C lds[Geo::G * Geo::LDS];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   int64_t u = blockIdx.x;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_tile_rows(
     const typename Complex<T>::type* __restrict__ tw) {
   using C = typename Complex<T>::type;
   using Geo = RowGeom<T, L>;
-  using F = BlockFft<T, L, Geo::E, -1>;
+  using F = BlockFft<T, L, Geo::E, -1, TW_MIXED>;
   __shared__ C lds[Geo::G * fft_lds_elems<T, L>()];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
   const int seg = static_cast<int>(blockIdx.x) * Geo::G + g;
