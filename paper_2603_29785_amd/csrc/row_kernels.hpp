@@ -204,39 +204,53 @@ __device__ __forceinline__ int opaque_copy(int v) {
 // a row's TPR threads holds. Lanes of one row inside a wave combine by an xor
 // butterfly (every lane ends with the same bits); rows spanning several waves
 // then add the per-wave results in wave order through `part` (LDS the
-// transform no longer reads, NT/64 elements). Every thread of the block must
-// call it.
-template <typename T, int E, int TPR, int NT>
+// transform no longer reads, H * NT / 64 elements). Every thread of the block
+// must call it.
+// H = 2: two-group rows. Registers come in runs of RL values (last radix), run
+// q at tl + q TPR, and a thread of the one-group form holds every second run:
+// those of parity h belong to its thread tl + h TPR. The sums are kept apart
+// by parity and combined in the waves and the wave order of the one-group
+// form, so a row's statistics have the same bits in both.
+template <typename T, int E, int TPR, int NT, int H, int RL>
 __device__ __forceinline__ void row_stats(const typename Complex<T>::type (&v)[E], int tl, bool ok,
                                           typename Complex<T>::type* __restrict__ dst,
                                           typename Complex<T>::type* __restrict__ part) {
   using C = typename Complex<T>::type;
+  static_assert(H == 1 || (TPR >= 64 && E % (2 * RL) == 0), "whole waves and runs in pairs");
   constexpr int W = TPR < 64 ? TPR : 64;     // lanes of a row within one wave
   constexpr int WPR = TPR > 64 ? TPR / 64 : 1;
-  T e = 0, m = 0;
+  T e[H] = {}, m[H] = {};
 #pragma unroll
   for (int i = 0; i < E; ++i) {
+    const int h = (i / RL) % H;
     const T a = v[i].x * v[i].x + v[i].y * v[i].y;
-    e += a;
-    m = fmax(m, a);
+    e[h] += a;
+    m[h] = fmax(m[h], a);
   }
 #pragma unroll
-  for (int o = 1; o < W; o <<= 1) {
-    e += __shfl_xor(e, o, W);
-    m = fmax(m, __shfl_xor(m, o, W));
+  for (int h = 0; h < H; ++h) {
+#pragma unroll
+    for (int o = 1; o < W; o <<= 1) {
+      e[h] += __shfl_xor(e[h], o, W);
+      m[h] = fmax(m[h], __shfl_xor(m[h], o, W));
+    }
   }
   if constexpr (WPR == 1) {
-    if (ok && tl == 0) *dst = C{e, m};
+    if (ok && tl == 0) *dst = H == 1 ? C{e[0], m[0]} : C{e[0] + e[H - 1], fmax(m[0], m[H - 1])};
   } else {
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = C{e, m};
+    const int wave = threadIdx.x >> 6, w = tl >> 6;
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int h = 0; h < H; ++h) part[H * (wave - w) + h * WPR + w] = C{e[h], m[h]};
+    }
     __syncthreads();
     if (ok && tl == 0) {
-      const C* pr = part + (threadIdx.x >> 6);
+      const C* pr = part + H * wave;
       C r = pr[0];
 #pragma unroll
-      for (int w = 1; w < WPR; ++w) {
-        r.x += pr[w].x;
-        r.y = fmax(r.y, pr[w].y);
+      for (int i = 1; i < H * WPR; ++i) {
+        r.x += pr[i].x;
+        r.y = fmax(r.y, pr[i].y);
       }
       *dst = r;
     }
@@ -391,7 +405,7 @@ __global__ __launch_bounds__((RowsGeom<T, L, WIDE>::NT), (WIDE ? 4 : 1)) void k_
   } else {
 #pragma unroll
     for (int i = 0; i < Geo::E; ++i) bstore<C, kYStore>(ry, v[i], vb, F::out_off(i) * sizeof(C));
-    if constexpr (STATS) row_stats<T, Geo::E, Geo::TPR, Geo::NT>(v, tl, ok, stats + gr, lds);
+    if constexpr (STATS) row_stats<T, Geo::E, Geo::TPR, Geo::NT, WIDE ? 2 : 1, F::RL>(v, tl, ok, stats + gr, lds);
   }
 }
 

@@ -57,3 +57,25 @@ def test_both_forms_same_bits(case):
     # the dual frame amplifies rounding by up to sqrt(kappa); the bar is stated for kappa <= 1e4
     kappa = p.info.frame_B / p.info.frame_A
     assert e <= TOL[precision] and ex <= TOL[precision] * max(1.0, (kappa / 1e4) ** 0.5), (e, ex)
+
+
+@pytest.mark.parametrize("case", CASES, ids=["%s_%d" % (c[0], c[5]) for c in CASES])
+def test_row_statistics_same_bits(case):
+    """The row statistics of a segment have the same bits alone, in a batch
+    whose rows take the two-group form, and in that batch under a workspace
+    that cuts it into chunks of the one-group form."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_29785_amd as qt
+    precision, fs, n, q, R, n_out, B = case
+    print("case", case, flush=True)
+    p = qt.Plan(fs, n, q, 10.0, fs / 2, R, n_out=n_out, precision=precision)
+    rdt = torch.float64 if precision == "fp64" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(7 * n_out)
+    x = torch.randn((B, n), generator=gen, device="cuda", dtype=rdt)
+    m = p.forward_metric(x)[1]
+    small = torch.empty(p.workspace_bytes(1), dtype=torch.uint8, device="cuda")
+    assert torch.equal(p.forward_metric(x, ws=small)[1], m)
+    for i in (0, B - 1):
+        assert torch.equal(p.forward_metric(x[i:i + 1])[1], m[i:i + 1])
