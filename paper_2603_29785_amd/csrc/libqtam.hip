@@ -862,9 +862,21 @@ bool launch_inv_rows_rowst(int log2l1, const void* A, void* S, const RowMeta* ro
   }
 }
 
+// Whether a segment's N/2 = radix_r * M2 values fit one workgroup (as SegGeom:
+// LDS for radix_r padded regions, at most 1024 threads).
+bool one_workgroup(const qtam_plan_s* pl) {
+  const bool f64 = pl->hp.precision == QTAM_FP64;
+  const int64_t r = pl->radix_r, threads = r * (pl->m2 / engine_e(pl->m2, f64));
+  return !pl->four_step && threads <= 1024 &&
+         (threads < 256 || size_t(r) * size_t(lds_size(static_cast<int>(pl->m2))) * (f64 ? 16 : 8) <= 160u * 1024u);
+}
+
 // ---------------------------------------------------------------------------
 // Workspace layout for a chunk of segments
 // ---------------------------------------------------------------------------
+// spec: half spectrum; tmp: between the passes of two-pass transforms; tmp2:
+// decimated rows of segments beyond one workgroup; pack: kept slots; rows:
+// long rows between their passes.
 struct WsLayout {
   size_t spec = 0, tmp = 0, tmp2 = 0, pack = 0, rows = 0, total = 0;
 };
@@ -876,9 +888,9 @@ WsLayout layout_for(const qtam_plan_s* pl, int64_t segs) {
   w.spec = off;
   off = align256(off + size_t(segs) * size_t(pl->hp.half) * cb);
   w.tmp = off;
-  if (pl->four_step || pl->radix_r > 1) off = align256(off + size_t(segs) * size_t(pl->hp.half) * cb);
+  if (pl->four_step) off = align256(off + size_t(segs) * size_t(pl->hp.half) * cb);
   w.tmp2 = off;
-  if (pl->radix_r > 1) off = align256(off + size_t(segs) * size_t(pl->hp.half) * cb);
+  if (pl->radix_r > 1 && !one_workgroup(pl)) off = align256(off + size_t(segs) * size_t(pl->hp.half) * cb);
   w.pack = off;
   off = align256(off + size_t(segs) * size_t(pl->hp.sum_len) * cb);
   w.rows = off;
@@ -946,21 +958,12 @@ bool transform_m2(qtam_plan_s* pl, const void* in, void* out, void* tmp, int64_t
   return launch_fft_rows_t<T, S, kPass2E, ROUT>(ilog2(pl->n1), tmp, out, pl->n2, count, m2, pl->d_tw_n1, st);
 }
 
-// Whether a segment's N/2 = R * M2 values fit one workgroup (as SegGeom: LDS
-// for R padded regions, at most 1024 threads).
-template <typename T, int R>
-bool one_workgroup(const qtam_plan_s* pl) {
-  const int64_t tpr = pl->m2 / engine_e(pl->m2, sizeof(T) == 8);
-  return !pl->four_step && R * tpr <= 1024 &&
-         (R * tpr < 256 || size_t(R) * size_t(lds_size(static_cast<int>(pl->m2))) * 2 * sizeof(T) <= 160u * 1024u);
-}
-
 // Spectrum of segments with N/2 = R * M2: in one workgroup, or the decimated
 // transforms (x -> rows `f`) and the combination with the twist.
 template <typename T, int R>
 bool spectrum_r(qtam_plan_s* pl, const void* x, void* spec, void* f, void* tmp, int64_t segs, hipStream_t st) {
   using C = typename Complex<T>::type;
-  if (one_workgroup<T, R>(pl)) {
+  if (one_workgroup(pl)) {
     Timed tm(pl, K_SPEC, st);
     return launch_seg<T, -1, R>(ilog2(pl->m2), x, spec, segs, pl->d_tw_half, tw2_of<T>(pl), st);
   }
@@ -980,7 +983,7 @@ bool spectrum_r(qtam_plan_s* pl, const void* x, void* spec, void* f, void* tmp, 
 template <typename T, int R>
 bool synthesis_r(qtam_plan_s* pl, const void* spec, void* x, void* a, void* tmp, int64_t segs, hipStream_t st) {
   using C = typename Complex<T>::type;
-  if (one_workgroup<T, R>(pl)) {
+  if (one_workgroup(pl)) {
     Timed tm(pl, K_SYN, st);
     return launch_seg<T, +1, R>(ilog2(pl->m2), spec, x, segs, pl->d_tw_half, tw2_of<T>(pl), st);
   }
@@ -1280,9 +1283,11 @@ int64_t dense_chunk_cap(const qtam_plan_s* pl) {
   return cap;
 }
 
+// The transform layout, and the tiles between the passes of two-pass tiles.
 size_t dense_ws_bytes(const qtam_plan_s* pl, int64_t segs) {
   const size_t cb = pl->hp.precision == QTAM_FP64 ? 16 : 8;
-  return align256(layout_for(pl, segs).total) + size_t(segs) * size_t(pl->hp.rows) * size_t(pl->hp.n) * cb;
+  const size_t base = layout_for(pl, segs).total;
+  return pl->dense_four_step ? align256(base) + size_t(segs) * size_t(pl->hp.rows) * size_t(pl->hp.n) * cb : base;
 }
 
 // Single-tile recovery of row `row`: its N_out-point forward transform in one
@@ -1984,7 +1989,7 @@ qtam_status qtam_dense(qtam_plan_t pl, const void* y, void* dense, int64_t batch
     const int64_t segs = std::min(chunk, batch - b0);
     const WsLayout lay = layout_for(pl, segs);
     char* w = static_cast<char*>(ws);
-    void* dtmp = w + align256(lay.total);
+    void* dtmp = pl->dense_four_step ? w + align256(lay.total) : nullptr;
     const char* src = static_cast<const char*>(y) + size_t(b0) * size_t(hp.rows) * size_t(hp.n_out) * cb;
     char* dst = static_cast<char*>(dense) + size_t(b0) * size_t(hp.rows) * size_t(hp.n) * cb;
     const bool ok = f64 ? run_dense<double>(pl, src, dst, segs, w, lay, dtmp, st)
