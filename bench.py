@@ -111,10 +111,11 @@ def measured_traffic(kernel: str, batch: int):
 
 
 def long_rows(plan) -> bool:
-    """Envelope rows longer than one workgroup's transform go through two
-    passes (the first forward pass and the second inverse pass then move only
-    the intermediate)."""
-    return plan.N_out > (8192 if plan.fp64 else 32768)
+    """Envelope rows of a power-of-two length beyond one workgroup's transform
+    go through two passes (the first forward pass and the second inverse pass
+    then move only the intermediate); chirp-z rows are one kernel kind at any
+    length."""
+    return plan.N_out > (8192 if plan.fp64 else 32768) and plan.N_out & (plan.N_out - 1) == 0
 
 
 def kernel_bytes(kind: str, plan, batch: int, b: int):
@@ -126,18 +127,15 @@ def kernel_bytes(kind: str, plan, batch: int, b: int):
     N, R, no = plan.N, plan.R, plan.N_out
     x, y = N * b, R * no * 2 * b
     two = long_rows(plan)
-    # N/2 = 3 2^k or 5 2^k: a permutation kernel reads the signal and another
-    # writes the reconstruction; the power-of-two transforms between move
-    # intermediates only
-    dec = (N // 2) & (N // 2 - 1) != 0
-    xt = 0 if dec else x
     per_seg = {
-        "spectrum_fft": xt, "spectrum_fft_pass1": xt, "spectrum_permute": x,    # read the signal
-        "spectrum_fft_pass2": 0, "spectrum_twist": 0, "spectrum_radix": 0,
+        "spectrum_fft": x, "spectrum_fft_pass1": x,                             # read the signal
+        "spectrum_fft_pass2": 0, "spectrum_radix": 0,
         "fwd_rows": 0 if two else y, "fwd_rows_pass2": y if two else 0,        # write the envelopes
         "inv_rows": y, "inv_rows_pass2": 0,                                     # read the envelopes
         "overlap_add": 0, "synthesis_radix": 0, "synthesis_fft_pass1": 0,
-        "synthesis_fft": xt, "synthesis_fft_pass2": xt, "synthesis_permute": x,  # write the reconstruction
+        "synthesis_fft": x, "synthesis_fft_pass2": x,                           # write the reconstruction
+        # passes that only permute or twist move intermediates
+        "spectrum_twist": 0, "spectrum_permute": 0, "synthesis_permute": 0,
     }.get(kind)
     return None if per_seg is None else float(per_seg) * batch
 

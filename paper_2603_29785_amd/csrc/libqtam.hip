@@ -50,18 +50,14 @@ using namespace qtam;
 
 namespace {
 
-enum Kind { K_SPEC = 0, K_SPEC1, K_SPEC2, K_TWIST, K_FWD_ROWS, K_FWD_ROWS2, K_INV_ROWS, K_INV_ROWS2, K_OLA,
-            K_SYN, K_SYN1, K_SYN2, K_ROW_STATS, K_PLANE_BEST, K_GATHER, K_SPEC_PERM, K_SPEC_RADIX, K_SYN_RADIX,
-            K_SYN_PERM, K_DENSE_PLACE, K_DENSE_FFT, K_DENSE_FFT1, K_DENSE_FFT2, K_DENSE_RADIX, K_DENSE_PERM,
-            K_MASK_FWD, K_MASK_BWD, K_NUM };
-const char* const kKindName[K_NUM] = {"spectrum_fft", "spectrum_fft_pass1", "spectrum_fft_pass2",
-                                       "spectrum_twist", "fwd_rows", "fwd_rows_pass2", "inv_rows",
-                                       "inv_rows_pass2", "overlap_add", "synthesis_fft",
-                                       "synthesis_fft_pass1", "synthesis_fft_pass2", "row_stats",
-                                       "plane_best", "gather_plane", "spectrum_permute", "spectrum_radix",
-                                       "synthesis_radix", "synthesis_permute", "dense_place", "dense_fft",
-                                       "dense_fft_pass1", "dense_fft_pass2", "dense_radix", "dense_permute",
-                                       "mask_forward", "mask_backward"};
+enum Kind { K_SPEC = 0, K_SPEC1, K_SPEC2, K_SPEC_RADIX, K_FWD_ROWS, K_FWD_ROWS2, K_INV_ROWS, K_INV_ROWS2, K_OLA,
+            K_SYN, K_SYN1, K_SYN2, K_SYN_RADIX, K_ROW_STATS, K_PLANE_BEST, K_GATHER, K_DENSE_FFT, K_DENSE_FFT1,
+            K_DENSE_FFT2, K_MASK_FWD, K_MASK_BWD, K_NUM };
+const char* const kKindName[K_NUM] = {"spectrum_fft", "spectrum_fft_pass1", "spectrum_fft_pass2", "spectrum_radix",
+                                       "fwd_rows", "fwd_rows_pass2", "inv_rows", "inv_rows_pass2", "overlap_add",
+                                       "synthesis_fft", "synthesis_fft_pass1", "synthesis_fft_pass2",
+                                       "synthesis_radix", "row_stats", "plane_best", "gather_plane", "dense_fft",
+                                       "dense_fft_pass1", "dense_fft_pass2", "mask_forward", "mask_backward"};
 
 enum Table { T_FWD = 0, T_DUAL = 1, T_AFWD = 2, T_AINV = 3, T_DENSE = 4, T_TILE = 5 };
 
