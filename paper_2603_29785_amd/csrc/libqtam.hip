@@ -181,10 +181,31 @@ namespace {
 // ---------------------------------------------------------------------------
 // Table construction for the device
 // ---------------------------------------------------------------------------
+// e^{2 pi i p / q}, within 0.51 units in the last place per component: the
+// angle is brought into [0, pi/4] with integers, and what its rounding to
+// double leaves out is added to first order.
+std::complex<double> unit_root(int64_t p, int64_t q) {
+  p %= q;
+  if (p < 0) p += q;
+  int64_t e = 8 * p;                       // eighths of a turn times q
+  const bool neg = e > 4 * q;              // lower half plane: conjugate of q - p
+  if (neg) e = 8 * q - e;
+  const bool left = e > 2 * q;             // second quadrant: minus the conjugate
+  if (left) e = 4 * q - e;
+  const bool swap = e > q;                 // above pi/4: parts exchanged
+  if (swap) e = 2 * q - e;
+  const long double al = 0.78539816339744830961566L * static_cast<long double>(e) / static_cast<long double>(q);
+  const double a = static_cast<double>(al), r = static_cast<double>(al - a);
+  const double s0 = std::sin(a), c0 = std::cos(a);
+  double c = c0 - r * s0, s = s0 + r * c0;
+  if (swap) std::swap(c, s);
+  return {left ? -c : c, neg ? -s : s};
+}
+
 // In-place forward DFT (e^{-2 pi i k n / L}) of a power-of-two length in
-// FP64 on the host: bit reversal, then butterflies with every twiddle from
-// its own angle (those of the last stage, which hold the others).
-void host_fft(std::vector<std::complex<double>>& a) {
+// FP64 on the host: bit reversal, then butterflies with the twiddles of the
+// last stage, w[k] = e^{-2 pi i k / L}, k < L / 2 (they hold the others).
+void host_fft(std::vector<std::complex<double>>& a, const std::vector<std::complex<double>>& w) {
   const int64_t n = static_cast<int64_t>(a.size());
   for (int64_t i = 1, j = 0; i < n; ++i) {
     int64_t bit = n >> 1;
@@ -192,9 +213,6 @@ void host_fft(std::vector<std::complex<double>>& a) {
     j ^= bit;
     if (i < j) std::swap(a[i], a[j]);
   }
-  std::vector<std::complex<double>> w(n / 2);
-  for (int64_t k = 0; k < n / 2; ++k)
-    w[k] = std::polar(1.0, -2.0 * M_PI * static_cast<double>(k) / static_cast<double>(n));
   for (int64_t len = 2; len <= n; len <<= 1)
     for (int64_t i = 0; i < n; i += len)
       for (int64_t k = 0; k < len / 2; ++k) {
@@ -238,6 +256,71 @@ void stockham_twiddles(std::vector<T>& out, int64_t L, int64_t e, int mode = TW_
       }
   }
   if (out.empty()) out.assign(2, T(0));
+}
+
+// The overlap-save rows' table, in the same order: base powers, each within
+// half a unit in the last place of its value.
+template <typename T>
+void stockham_roots(std::vector<T>& out, int64_t L, int64_t e) {
+  out.clear();
+  const int64_t rmax = std::min<int64_t>(e, 16);
+  for (int64_t ns = rmax; ns < L;) {
+    const int64_t R = std::min(rmax, L / ns);
+    for (int64_t r = 1; r < R; r *= 2)
+      for (int64_t k = 0; k < ns; ++k) {
+        const std::complex<double> w = unit_root(-r * k, ns * R);
+        out.push_back(static_cast<T>(w.real()));
+        out.push_back(static_cast<T>(w.imag()));
+      }
+    ns *= R;
+  }
+}
+
+// Mean gain of the block transform whose table `tw` (stockham_roots) gives: the
+// mean over inputs and outputs of its factors over the exact ones, with the
+// butterflies' constants rounded to T and the twiddles formed in T from the
+// base powers (BlockFft::load_twiddles). Below 1 by 2e-8 per pass in FP32, a
+// part of the error that does not average out as rounding does; a table that
+// multiplies the transform's values takes it back out.
+template <typename T>
+double transform_gain(const std::vector<T>& tw, int64_t L, int64_t e) {
+  using Z = std::complex<double>;
+  const int64_t rmax = std::min<int64_t>(e, 16);
+  const double r2 = static_cast<T>(Root16::r2), c1 = static_cast<T>(Root16::c1), t1 = static_cast<T>(Root16::t1);
+  const double g45 = r2 * std::sqrt(2.0);                                          // rotations by pi/4, 3 pi/4
+  const double g22 = c1 * (std::cos(M_PI / 8.0) + t1 * std::sin(M_PI / 8.0));      // by odd multiples of pi/8
+  auto butterfly = [&](int64_t R) {
+    return R >= 16 ? (8.0 + 4.0 * g45 + 4.0 * g22) / 16.0 : R >= 8 ? (6.0 + 2.0 * g45) / 8.0 : 1.0;
+  };
+  struct W { T x, y; };
+  auto mul = [](W a, W b) { return W{std::fma(a.x, b.x, -(a.y * b.y)), std::fma(a.x, b.y, a.y * b.x)}; };
+  double gain = butterfly(std::min(rmax, L));
+  size_t at = 0;
+  for (int64_t ns = rmax; ns < L;) {
+    const int64_t R = std::min(rmax, L / ns);
+    double sum = static_cast<double>(ns);   // r = 0
+    int64_t slots = 0;
+    for (int64_t r = 1; r < R; r *= 2) ++slots;
+    for (int64_t k = 0; k < ns; ++k) {
+      W a[16] = {};
+      for (int64_t sl = 0; sl < slots; ++sl) {
+        const T* w = &tw[at + 2 * (sl * ns + k)];
+        a[int64_t(1) << sl] = W{w[0], w[1]};
+      }
+      if (R > 2) a[3] = mul(a[2], a[1]);
+      if (R > 4) {
+        a[5] = mul(a[4], a[1]);
+        a[6] = mul(a[4], a[2]);
+        a[7] = mul(a[4], a[3]);
+      }
+      for (int64_t r = 9; r < R; ++r) a[r] = mul(a[8], a[r - 8]);
+      for (int64_t r = 1; r < R; ++r) sum += (Z(a[r].x, a[r].y) * std::conj(unit_root(-r * k, ns * R))).real();
+    }
+    gain *= butterfly(R) * sum / static_cast<double>(ns * R);
+    at += 2 * static_cast<size_t>(slots * ns);
+    ns *= R;
+  }
+  return gain;
 }
 
 // Values per thread of a length-L block transform (as RowGeom: at most 1024
@@ -302,7 +385,7 @@ qtam_status upload(qtam_plan_s* pl) {
   const std::vector<double>* src[6] = {&hp.fwd_tab, &hp.dual_tab, &hp.afwd_tab, &hp.ainv_tab, &dense_tab,
                                        &hp.tile_tab};
   auto chirp = [&](int64_t v) {   // e^{+pi i v^2 / N_out}, v^2 reduced mod 2 N_out exactly
-    return std::polar(1.0, M_PI * static_cast<double>((v * v) % (2 * int64_t(hp.n_out))) / static_cast<double>(hp.n_out));
+    return unit_root((v * v) % (2 * int64_t(hp.n_out)), 2 * int64_t(hp.n_out));
   };
   std::vector<std::complex<double>> row_chirp;   // by |c - centre|
   if (pl->bs_os) {
@@ -367,24 +450,32 @@ qtam_status upload(qtam_plan_s* pl) {
   size_t o_bsc = 0, o_bsf = 0, o_bsi = 0, o_bstw = 0, o_osb = 0;
   if (pl->bs_os) {
     const int64_t M = hp.n_out, Lb = pl->bs_len;
+    const int64_t jn = Lb - pl->os.JP - pl->os.B;   // largest negative offset of any row
     std::vector<T> ta(2 * M), tb(2 * size_t(pl->os.nmax) * size_t(Lb));
+    std::vector<std::complex<double>> lag(std::max<int64_t>(M + jn, pl->os.JP + 1));   // the chirp by |lag|
+    for (size_t v = 0; v < lag.size(); ++v) lag[v] = chirp(static_cast<int64_t>(v));
     for (int64_t v = 0; v < M; ++v) {
-      const std::complex<double> a = chirp(v);
-      ta[2 * v] = static_cast<T>(a.real());
-      ta[2 * v + 1] = static_cast<T>(a.imag());
+      ta[2 * v] = static_cast<T>(lag[v].real());
+      ta[2 * v + 1] = static_cast<T>(lag[v].imag());
     }
-    std::vector<std::complex<double>> seg(Lb);
-    for (int64_t i = 0; i < pl->os.nmax; ++i) {   // lags V_i .. V_i + L - 1
-      for (int64_t u = 0; u < Lb; ++u) seg[u] = std::conj(chirp(i * pl->os.B - pl->os.JP + u));
-      host_fft(seg);
+    stockham_roots(tw, Lb, engine_e(Lb, f64));
+    const double gain = transform_gain(tw, Lb, engine_e(Lb, f64)),
+                 scale = 1.0 / (static_cast<double>(Lb) * gain * gain);
+    std::vector<std::complex<double>> seg(Lb), roots(Lb / 2);
+    for (int64_t k = 0; k < Lb / 2; ++k) roots[k] = unit_root(-k, Lb);
+    for (int64_t i = 0; i < pl->os.nmax; ++i) {   // lags V_i .. V_i + L - 1, zero beyond the last one any output needs
+      for (int64_t u = 0; u < Lb; ++u) {
+        const int64_t v = i * pl->os.B - pl->os.JP + u;
+        seg[u] = v < M + jn ? std::conj(lag[v < 0 ? -v : v]) : 0.0;
+      }
+      host_fft(seg, roots);
       for (int64_t k = 0; k < Lb; ++k) {
-        tb[2 * (i * Lb + k)] = static_cast<T>(seg[k].real() / static_cast<double>(Lb));
-        tb[2 * (i * Lb + k) + 1] = static_cast<T>(seg[k].imag() / static_cast<double>(Lb));
+        tb[2 * (i * Lb + k)] = static_cast<T>(seg[k].real() * scale);
+        tb[2 * (i * Lb + k) + 1] = static_cast<T>(seg[k].imag() * scale);
       }
     }
     o_bsc = blob.add(ta.data(), ta.size() * sizeof(T));
     o_bsf = blob.add(tb.data(), tb.size() * sizeof(T));
-    stockham_twiddles(tw, Lb, engine_e(Lb, f64));
     o_bstw = blob.add(tw.data(), tw.size() * sizeof(T));
     o_osb = blob.add(pl->os_blocks.data(), pl->os_blocks.size() * sizeof(int));
   } else if (pl->bluestein) {
@@ -402,8 +493,11 @@ qtam_status upload(qtam_plan_s* pl) {
         bi[Lb - v] = a[v];
       }
     }
-    host_fft(bf);
-    host_fft(bi);
+    std::vector<std::complex<double>> roots(Lb / 2);
+    for (int64_t k = 0; k < Lb / 2; ++k)
+      roots[k] = std::polar(1.0, -2.0 * M_PI * static_cast<double>(k) / static_cast<double>(Lb));
+    host_fft(bf, roots);
+    host_fft(bi, roots);
     std::vector<T> ta(2 * M), tf(2 * Lb), ti(2 * Lb);
     for (int64_t v = 0; v < M; ++v) {
       ta[2 * v] = static_cast<T>(a[v].real());
