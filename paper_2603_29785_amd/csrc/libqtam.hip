@@ -868,8 +868,8 @@ bool launch_rows_bs(bool forward, int log2l, const void* in, void* out, const Ro
 
 // Forward rows: a workgroup per row and block while all of them are resident
 // at once (four per CU); one segment of 62 rows and 12289 values, say.
-int os_grid_y(const qtam_plan_s* pl, int blocks) {
-  return int64_t(blocks) * pl->os.nmax <= 4 * int64_t(pl->num_cus) ? pl->os.nmax : 1;
+bool os_one_block(const qtam_plan_s* pl, int blocks) {
+  return int64_t(blocks) * pl->os.nmax <= 4 * int64_t(pl->num_cus);
 }
 
 template <typename T>
@@ -884,19 +884,27 @@ bool launch_rows_os(bool forward, qtam_plan_s* pl, const void* in, void* out, in
                   (LG) <= (sizeof(T) == 4 ? kMaxLog2Os32 : kMaxLog2Os64)) {                              \
       using Geo = RowGeom<T, (1 << LG)>;                                                               \
       const int blocks = static_cast<int>((total_rows + Geo::G - 1) / Geo::G);                         \
-      if (forward)                                                                                     \
-        hipLaunchKernelGGL((k_fwd_rows_os<T, (1 << LG)>),                                              \
-                           dim3(unsigned(blocks), unsigned(os_grid_y(pl, blocks))), dim3(Geo::NT), 0, st, \
+      if (forward) {                                                                                   \
+        const bool one = os_one_block(pl, blocks);                                                     \
+        auto kern = one ? k_fwd_rows_os<T, (1 << LG), true> : k_fwd_rows_os<T, (1 << LG), false>;      \
+        hipLaunchKernelGGL(kern, dim3(unsigned(blocks), unsigned(one ? pl->os.nmax : 1)), dim3(Geo::NT), 0, st, \
                            static_cast<const C*>(in), static_cast<C*>(out), pl->d_rows,                \
                            static_cast<const C*>(pl->d_tab[table]), hp.rows, int(total_rows),          \
                            int(hp.half), pl->os, static_cast<const C*>(pl->d_bs_chirp),                \
                            static_cast<const C*>(pl->d_bs_bf), static_cast<const C*>(pl->d_bs_tw), blocks); \
-      else                                                                                             \
-        hipLaunchKernelGGL((k_inv_rows_os<T, (1 << LG)>), dim3(unsigned(blocks)), dim3(Geo::NT), 0, st,  \
-                           static_cast<const C*>(in), static_cast<C*>(out), pl->d_rows,                \
-                           static_cast<const C*>(pl->d_tab[table]), hp.rows, int(total_rows),          \
-                           int(hp.sum_len), pl->os, static_cast<const C*>(pl->d_bs_chirp),             \
-                           static_cast<const C*>(pl->d_bs_bf), static_cast<const C*>(pl->d_bs_tw));    \
+        return true;                                                                                   \
+      }                                                                                                \
+      constexpr int PB = os_side_by_side<T, (1 << LG)>(), P2 = PB > 1 ? 2 : 1;                         \
+      const int pb = pl->os.nmax == 1 || total_rows > pl->num_cus ? 1 : pl->os.nmax == 2 ? P2 : PB;    \
+      auto kern = pb == 1   ? k_inv_rows_os<T, (1 << LG), 1>                                           \
+                  : pb == 2 ? k_inv_rows_os<T, (1 << LG), P2>                                          \
+                            : k_inv_rows_os<T, (1 << LG), PB>;                                         \
+      hipLaunchKernelGGL(kern, dim3(unsigned(pb == 1 ? blocks : total_rows)),                          \
+                         dim3(pb == 1 ? Geo::NT : pb * Geo::TPR), 0, st,                               \
+                         static_cast<const C*>(in), static_cast<C*>(out), pl->d_rows,                  \
+                         static_cast<const C*>(pl->d_tab[table]), hp.rows, int(total_rows),            \
+                         int(hp.sum_len), pl->os, static_cast<const C*>(pl->d_bs_chirp),               \
+                         static_cast<const C*>(pl->d_bs_bf), static_cast<const C*>(pl->d_bs_tw));      \
       return true;                                                                                     \
     }                                                                                                  \
     return false;

@@ -685,8 +685,9 @@ constexpr int os_in_reg(int i) {
   return -1;
 }
 
-template <typename T, int L>
-__global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
+// ONE: a workgroup per row and block (blockIdx.y), for few rows.
+template <typename T, int L, bool ONE>
+__global__ __launch_bounds__((RowGeom<T, L>::NT), (ONE ? 1 : 4)) void k_fwd_rows_os(
     const typename Complex<T>::type* __restrict__ spec, typename Complex<T>::type* __restrict__ Y,
     const RowMeta* __restrict__ rows, const typename Complex<T>::type* __restrict__ tab, int R, int total, int half, OsPlan os,
     const typename Complex<T>::type* __restrict__ chirp, const typename Complex<T>::type* __restrict__ bhat,
@@ -716,7 +717,10 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
     // (window and chirp); slots outside the support read 0
     const C* Z = spec + int64_t(seg) * half;
     const C z0 = Z[0];   // (X[0], X[N/2])
-    const rsrc_t rz = make_rsrc(Z + rm.lo, static_cast<uint32_t>((ok && rm.hi == half ? len - 1 : len) * sizeof(C)));
+    // (the entries below Nyquist; kept in a scalar register, else every load
+    // of the gather becomes a loop over lanes that waits for it)
+    const int zlen = __builtin_amdgcn_readfirstlane(ok && rm.hi == half ? len - 1 : len);
+    const rsrc_t rz = make_rsrc(Z + rm.lo, static_cast<uint32_t>(zlen * sizeof(C)));
     const rsrc_t rt = make_rsrc(tab + rm.off, static_cast<uint32_t>(len * sizeof(C)));
     unsigned bx = static_cast<unsigned>(tl - jlo) * static_cast<unsigned>(sizeof(C));   // d = c - lo of offset 0
     opaque(bx);
@@ -752,10 +756,10 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
   const rsrc_t rb = make_rsrc(bhat, static_cast<uint32_t>(os.nmax * L * int(sizeof(C))));
   // all blocks of the rows, or (few rows: the input transform repeated instead
   // of a workgroup's blocks in series) the one of blockIdx.y
-  const int b0 = gridDim.y > 1 ? static_cast<int>(blockIdx.y) : 0, b1 = gridDim.y > 1 ? b0 + 1 : nb;
+  const int b0 = ONE ? static_cast<int>(blockIdx.y) : 0, b1 = ONE ? b0 + 1 : nb;
   int done = b0 == 0 ? 0 : (b0 - 1) * os.B - os.JP + L + jlo;   // outputs stored by the blocks before
   for (int b = b0; b < b1; ++b) {
-    const int tb = opaque_copy(tl);   // keeps the transform's table loads in the loop (registers)
+    const int tb = ONE ? tl : opaque_copy(tl);   // keeps the transform's table loads in the loop (registers)
     C z[Geo::E];
 #pragma unroll
     for (int i = 0; i < Geo::E; ++i) {
@@ -783,8 +787,22 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_fwd_rows_os(
   }
 }
 
-template <typename T, int L>
-__global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_inv_rows_os(
+// PB > 1: one row per workgroup, whose PB thread groups transform PB blocks
+// side by side; then each group adds up the blocks for its share of the
+// registers, in the order of the blocks, so the bits are those of one group
+// after the other. For launches of at most a row per CU, which otherwise wait
+// for one block after the other, and for transforms of at most 128 threads: a
+// group of 256 has a wave on every SIMD of its CU already, and four of them
+// there take as long as four in turn (62 rows of 12289 values, L = 4096: 26 us
+// in turn, 31 us side by side). Inverse rows in turn : side by side (: by one
+// convolution): FP32 8 rows of 3535 values 22 : 14 (: 15) us, 16 rows of 1537
+// values 14 : 11.3 (: 10.5) us, 8 rows of 2501 values 21 : 11 (: 15) us, in FP64
+// 25 : 13 (: 20) us.
+template <typename T, int L> constexpr int os_side_by_side() { return RowGeom<T, L>::TPR <= 128 ? 4 : 1; }
+
+template <typename T, int L, int PB>
+__global__ __launch_bounds__((PB > 1 ? PB * RowGeom<T, L>::TPR : RowGeom<T, L>::NT),
+                             (PB > 1 ? (PB * RowGeom<T, L>::TPR + 255) / 256 : 4)) void k_inv_rows_os(
     const typename Complex<T>::type* __restrict__ Y, typename Complex<T>::type* __restrict__ Sbuf,
     const RowMeta* __restrict__ rows, const typename Complex<T>::type* __restrict__ tab, int R, int total, int sum_len, OsPlan os,
     const typename Complex<T>::type* __restrict__ chirp, const typename Complex<T>::type* __restrict__ bhat,
@@ -794,29 +812,46 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_inv_rows_os(
   using F = BlockFft<T, L, Geo::E, -1>;
   using Fi = BlockFft<T, L, Geo::E, +1>;
   static_assert(Geo::TPR >= 64, "a wave holds one row");
-  __shared__ C lds[Geo::G * lds_size(L)];
+  constexpr int G = PB > 1 ? 1 : Geo::G;   // rows of a workgroup
+  __shared__ C lds[G * PB * lds_size(L)];
   const int t = threadIdx.x, g = t / Geo::TPR, tl = t % Geo::TPR;
+  const int pb = PB > 1 ? __builtin_amdgcn_readfirstlane(g) : 0;
   C* reg = lds + g * lds_size(L);
   const int u = static_cast<int>(blockIdx.x);
-  int gr = u * Geo::G + g;
+  int gr = u * G + (PB > 1 ? 0 : g);
   gr = __builtin_amdgcn_readfirstlane(gr);
   const bool ok = gr < total;
   const int seg = ok ? gr / R : 0;
   const RowMeta rm = rows[ok ? gr - seg * R : 0];
   const int len = ok ? rm.hi - rm.lo + 1 : 0;
   const int jlo = rm.lo - rm.s;
-  const int nb = __builtin_amdgcn_readfirstlane(os.blocks[(u * Geo::G) % R]);
+  const int nb = __builtin_amdgcn_readfirstlane(os.blocks[(u * G) % R]);
   const rsrc_t rc = make_rsrc(chirp, static_cast<uint32_t>(os.M * sizeof(C)));
   const rsrc_t rb = make_rsrc(bhat, static_cast<uint32_t>(os.nmax * L * int(sizeof(C))));
   const C* yrow = Y + int64_t(ok ? gr : 0) * os.M;
-  C acc[Geo::E];
+  auto end_of = [&](int b) {   // inputs of the blocks up to b
+    const int e = b * os.B - os.JP + L + jlo;
+    return e < os.M ? e : os.M;
+  };
+  constexpr int S = Geo::E / PB;   // registers that a group adds up: pb S .. pb S + S - 1
+  C acc[S];
 #pragma unroll
-  for (int i = 0; i < Geo::E; ++i) acc[i] = C{0, 0};
-  int done = 0;
-  for (int b = 0; b < nb; ++b) {
+  for (int j = 0; j < S; ++j) acc[j] = C{0, 0};
+  auto off_of = [&](int j) {   // F::out_off(pb S + j)
+    const int i = pb * S + j;
+    return i / F::RL * Geo::TPR + i % F::RL * (L / F::RL);
+  };
+  auto table = [&](int b, int j) {
+    return bload<C>(rb, static_cast<uint32_t>(tl) * sizeof(C), static_cast<uint32_t>(b * L + off_of(j)) * sizeof(C));
+  };
+  auto add = [&](int j, C x, C bh) {
+    const C h = c_conj(bh);
+    acc[j] = C{fmadd(x.x, h.x, fmadd(-x.y, h.y, acc[j].x)), fmadd(x.x, h.y, fmadd(x.y, h.x, acc[j].y))};
+  };
+  for (int b0 = 0; b0 < nb; b0 += PB) {
+    const int b = b0 + pb;
+    const int done = b == 0 ? 0 : end_of(b - 1), end = ok && b < nb ? end_of(b) : done;
     const int V = b * os.B - os.JP;
-    int end = V + L + jlo < os.M ? V + L + jlo : os.M;
-    if (!ok || end < done) end = done;
     unsigned bc = static_cast<unsigned>(V + tl) * static_cast<unsigned>(sizeof(C));
     unsigned by = static_cast<unsigned>(V + tl - done) * static_cast<unsigned>(sizeof(C));
     opaque(bc);
@@ -830,22 +865,46 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT), 4) void k_inv_rows_os(
     }
     F::run(v, reg, opaque_copy(tl), F::twiddles(tw));   // (table loads stay in the loop: registers)
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (PB == 1) {
 #pragma unroll
-    for (int i = 0; i < Geo::E; ++i) {
-      const C h = c_conj(bload<C>(rb, static_cast<uint32_t>(tl) * sizeof(C),
-                                  static_cast<uint32_t>(b * L + F::out_off(i)) * sizeof(C)));
-      acc[i] = C{fmadd(v[i].x, h.x, fmadd(-v[i].y, h.y, acc[i].x)), fmadd(v[i].x, h.y, fmadd(v[i].y, h.x, acc[i].y))};
+      for (int j = 0; j < S; ++j) add(j, v[j], table(b, j));
+    } else {
+#pragma unroll
+      for (int i = 0; i < Geo::E; ++i) reg[lds_pad(tl + F::out_off(i))] = v[i];
+      C h[PB][S];
+#pragma unroll
+      for (int q = 0; q < PB; ++q) {
+#pragma unroll
+        for (int j = 0; j < S; ++j) h[q][j] = table(b0 + q < nb ? b0 + q : b0, j);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < PB; ++q) {
+        if (b0 + q < nb) {
+#pragma unroll
+          for (int j = 0; j < S; ++j) add(j, lds[q * lds_size(L) + lds_pad(tl + off_of(j))], h[q][j]);
+        }
+      }
+      __syncthreads();
     }
-    done = end;
   }
   C z[Geo::E];
+  if constexpr (PB == 1) {
 #pragma unroll
-  for (int i = 0; i < Geo::E; ++i) {
-    constexpr auto in_reg = os_in_reg<F, Fi, Geo::E>;
-    z[in_reg(i)] = acc[i];
+    for (int i = 0; i < Geo::E; ++i) {
+      constexpr auto in_reg = os_in_reg<F, Fi, Geo::E>;
+      z[in_reg(i)] = acc[i];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < S; ++j) lds[lds_pad(tl + off_of(j))] = acc[j];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < Geo::E; ++i) z[i] = lds[lds_pad(tl + Fi::in_off(i))];
+    __syncthreads();
   }
   Fi::run(z, reg, tl, Fi::twiddles(tw));
-  if (!ok) return;
+  if (!ok || pb > 0) return;
   // slot j mod L holds the kept entry d = j - jlo; the table holds its
   // conjugate chirp too
   const rsrc_t rs = make_rsrc(Sbuf + int64_t(seg) * sum_len + rm.off, static_cast<uint32_t>(len * sizeof(C)));
