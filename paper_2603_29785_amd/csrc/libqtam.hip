@@ -715,7 +715,7 @@ bool launch_fft_rows_t(int log2l, const void* in, void* out, int64_t n2, int64_t
 // one workgroup (one_workgroup).
 template <typename T, int S, int R>
 bool launch_seg(int log2m2, const void* in, void* out, int64_t segs, const void* tw,
-                Twiddle2<typename Complex<T>::type> tw2, hipStream_t st) {
+                Twiddle2<typename Complex<T>::type> tw2, int num_cus, hipStream_t st) {
   using C = typename Complex<T>::type;
   switch (log2m2) {
 #define X(LG)                                                                                       \
@@ -723,6 +723,13 @@ bool launch_seg(int log2m2, const void* in, void* out, int64_t segs, const void*
     if constexpr ((LG) >= 3 && (LG) <= kMaxLog2Seg) {                                               \
       using Geo = SegGeom<T, (1 << LG), R>;                                                         \
       if constexpr (Geo::FITS) {                                                                    \
+        if constexpr (S > 0 && syn_siblings<T, (1 << LG), R>()) {                                   \
+          if (4 * segs * R <= 3 * num_cus) {   /* a CU for every sibling, and some over */          \
+            hipLaunchKernelGGL((k_syn_siblings<T, (1 << LG), R>), dim3(unsigned(segs * R)), dim3(Geo::TPR), 0, st, \
+                               static_cast<const C*>(in), static_cast<C*>(out), segs, static_cast<const C*>(tw), tw2); \
+            return true;                                                                            \
+          }                                                                                         \
+        }                                                                                           \
         const dim3 grid(unsigned((segs + Geo::G - 1) / Geo::G));                                    \
         if constexpr (S < 0)                                                                        \
           hipLaunchKernelGGL((k_spec_seg<T, (1 << LG), R>), grid, dim3(Geo::NT), 0, st,             \
@@ -1063,7 +1070,7 @@ bool spectrum_r(qtam_plan_s* pl, const void* x, void* spec, void* f, void* tmp, 
   using C = typename Complex<T>::type;
   if (one_workgroup(pl)) {
     Timed tm(pl, K_SPEC, st);
-    return launch_seg<T, -1, R>(ilog2(pl->m2), x, spec, segs, pl->d_tw_half, tw2_of<T>(pl), st);
+    return launch_seg<T, -1, R>(ilog2(pl->m2), x, spec, segs, pl->d_tw_half, tw2_of<T>(pl), pl->num_cus, st);
   }
   if constexpr (R > 1) {
     if (!transform_m2<T, -1, R>(pl, x, f, tmp, segs * R, st, K_SPEC, K_SPEC1, K_SPEC2)) return false;
@@ -1083,7 +1090,7 @@ bool synthesis_r(qtam_plan_s* pl, const void* spec, void* x, void* a, void* tmp,
   using C = typename Complex<T>::type;
   if (one_workgroup(pl)) {
     Timed tm(pl, K_SYN, st);
-    return launch_seg<T, +1, R>(ilog2(pl->m2), spec, x, segs, pl->d_tw_half, tw2_of<T>(pl), st);
+    return launch_seg<T, +1, R>(ilog2(pl->m2), spec, x, segs, pl->d_tw_half, tw2_of<T>(pl), pl->num_cus, st);
   }
   {
     Timed tm(pl, K_SYN_RADIX, st);

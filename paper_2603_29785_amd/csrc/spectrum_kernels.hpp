@@ -373,7 +373,12 @@ __global__ __launch_bounds__((SegGeom<T, M2, R>::NT)) void k_spec_seg(
   if (g >= ns) return;
   const C* rows = lds + g * R * lds_size(M2);
   C* dst = out + (s0 + g) * (R * M2);
-  for (int k2 = t - g * Geo::TS; k2 <= M2 / 2; k2 += Geo::TS) {
+  // unrolled, so that the twiddle loads of all rounds are in flight at once
+  constexpr int ROUNDS = (M2 / 2 + Geo::TS) / Geo::TS;
+#pragma unroll
+  for (int i = 0; i < ROUNDS; ++i) {
+    const int k2 = t - g * Geo::TS + i * Geo::TS;
+    if (i == ROUNDS - 1 && k2 > M2 / 2) break;
     C a[R], b[R];
 #pragma unroll
     for (int n = 0; n < R; ++n) {
@@ -420,6 +425,57 @@ __global__ __launch_bounds__((SegGeom<T, M2, R>::NT)) void k_syn_seg(
   if (!ok) return;
   C* dst = out + seg * (R * M2);
   for (int i = ts; i < R * M2; i += Geo::TS) dst[i] = rows[(i % R) * lds_size(M2) + lds_pad(i / R)];
+}
+
+// The synthesis transform of a few segments as R sibling workgroups each: one
+// decimated row n1 straight from the spectrum (every sibling reads all of it),
+// its transform, and the interleaved store, the same operations as above. A
+// workgroup that holds a segment of more than 512 threads has three or more
+// waves on a SIMD and is bound by its CU's vector ALU; the siblings take R CUs.
+// Whole inverse in a graph, 16 to 32 rows, one workgroup : siblings, us:
+// FP32 24576 samples, 1 / 4 / 32 / 84 segments  20.1 / 20.7 / 25.8 / 36.4 : 18.7 / 19.4 / 24.5 / 37.1
+// FP64 12288 samples                            17.9 / 18.8 / 24.3 / 33.6 : 15.7 / 16.6 / 22.1 / 32.5
+// FP32 20480 samples (R = 5, rows of two waves) 19.8 / 20.5 / 25.1 / 34.2 : 20.2 / 20.9 / 25.2 / 35.0
+// (with separate radix, transform and permutation passes 18.4 / 19.2 / 26.3 /
+// 41.1, 17.0 / 17.8 / 25.2 / 39.2 and 18.0 / 18.9 / 25.8 / 39.1).
+template <typename T, int M2, int R>
+constexpr bool syn_siblings() { return R > 1 && SegGeom<T, M2, R>::TS > 512 && !(sizeof(T) == 4 && R == 5); }
+
+template <typename T, int M2, int R>
+__global__ __launch_bounds__((RowGeom<T, M2>::TPR), 1) void k_syn_siblings(
+    const typename Complex<T>::type* __restrict__ in, typename Complex<T>::type* __restrict__ out, int64_t segs,
+    const typename Complex<T>::type* __restrict__ tw, Twiddle2<typename Complex<T>::type> tw2) {
+  using C = typename Complex<T>::type;
+  using Geo = RowGeom<T, M2>;
+  using F = BlockFft<T, M2, Geo::E, +1>;
+  __shared__ C lds[lds_size(M2)];
+  const int tl = threadIdx.x;
+  int64_t seg;
+  int n1;
+  sibling_block<R>(blockIdx.x, segs, seg, n1);
+  const C* src = in + seg * (R * M2);
+  // every load in flight before the first is used
+  C a[Geo::E][R], wf[Geo::E], wc[Geo::E], v[Geo::E];
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) {
+    const int k2 = tl + F::in_off(i), m = 2 * n1 * k2;
+#pragma unroll
+    for (int k1 = 0; k1 < R; ++k1) a[i][k1] = src[k2 + M2 * k1];
+    wf[i] = tw2.fine[m & ((1 << tw2.bits) - 1)];
+    wc[i] = tw2.coarse[m >> tw2.bits];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) {
+    v[i] = a[i][0];
+#pragma unroll
+    for (int k1 = 1; k1 < R; ++k1) v[i] = c_add(v[i], c_mul(a[i][k1], root_r<T, R>(n1 * k1 % R)));
+    if (n1 > 0) v[i] = c_mul(v[i], c_conj(c_mul(wf[i], wc[i])));
+  }
+  F::run(v, lds, tl, F::twiddles(tw));
+  C* dst = out + seg * (R * M2) + n1;
+#pragma unroll
+  for (int i = 0; i < Geo::E; ++i) dst[R * (tl + F::out_off(i))] = v[i];
 }
 
 }  // namespace qtam
