@@ -631,9 +631,10 @@ bool launch_fft_rows(int log2l, const void* in, void* out, int64_t count, int64_
   switch (log2l) {
 #define X(LG)                                                                                      \
   case LG:                                                                                         \
-    if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Single32 : kMaxLog2Single64)) {               \
+    if constexpr ((LG) >= 3 && (LG) <= kMaxLog2Seg) {                                              \
       using Geo = RowGeom<T, (1 << LG)>;                                                           \
-      if constexpr ((RIN == 1 && ROUT == 1) || Geo::G == 1) {                                      \
+      /* decimated: only segments beyond one workgroup (launch_seg takes the others) */            \
+      if constexpr (RIN * ROUT == 1 || (Geo::G == 1 && !SegGeom<T, (1 << LG), RIN * ROUT>::FITS)) { \
         const int64_t blocks = (count + Geo::G - 1) / Geo::G;                                      \
         hipLaunchKernelGGL((k_fft_rows<T, (1 << LG), S, RIN, ROUT>), dim3(unsigned(blocks)),       \
                            dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out),  \
@@ -648,7 +649,10 @@ bool launch_fft_rows(int log2l, const void* in, void* out, int64_t count, int64_
   }
 }
 
-#define QTAM_COL_CASES(X) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12)
+// Four-step sub-FFTs: transforms in two passes start at 2^14 (FP64) and 2^14 or
+// 2^15 (FP32), so both factors have at least 128 points and every number of
+// columns or rows per workgroup divides the other factor.
+#define QTAM_COL_CASES(X) X(7) X(8) X(9) X(10) X(11) X(12)
 constexpr int kMaxLog2Col32 = 12;   // four-step sub-FFTs up to 4096 points (FP32)
 constexpr int kMaxLog2Col64 = 11;   // and 2048 points (FP64)
 
@@ -660,16 +664,9 @@ bool launch_fft_cols(int log2l, const void* in, void* out, int64_t n1, int64_t s
 #define X(LG)                                                                                     \
   case LG:                                                                                        \
     if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Col32 : kMaxLog2Col64)) {                     \
-      using GeoW = ColGeom<T, (1 << LG), 0, kColWide>;                                            \
-      if (n1 % GeoW::CC == 0) {                                                                   \
-        hipLaunchKernelGGL((k_fft_cols<T, (1 << LG), S, kColWide, RIN>), dim3(unsigned(n1 / GeoW::CC), unsigned(segs)), \
-                           dim3(GeoW::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n1, \
-                           seg_stride, static_cast<const C*>(tw), tw2, tw_mul);                   \
-        return true;                                                                              \
-      }                                                                                           \
-      using Geo = ColGeom<T, (1 << LG)>;                                                          \
+      using Geo = ColGeom<T, (1 << LG), 0, kColWide>;                                             \
       if (n1 % Geo::CC) return false;                                                             \
-      hipLaunchKernelGGL((k_fft_cols<T, (1 << LG), S, 0, RIN>), dim3(unsigned(n1 / Geo::CC), unsigned(segs)), \
+      hipLaunchKernelGGL((k_fft_cols<T, (1 << LG), S, kColWide, RIN>), dim3(unsigned(n1 / Geo::CC), unsigned(segs)), \
                          dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n1, \
                          seg_stride, static_cast<const C*>(tw), tw2, tw_mul);                     \
       return true;                                                                                \
@@ -690,17 +687,10 @@ bool launch_fft_rows_t(int log2l, const void* in, void* out, int64_t n2, int64_t
   case LG:                                                                                          \
     if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Col32 : kMaxLog2Col64)) {                       \
       constexpr int CW = EP == 0 ? kRowWide : 0;                                                    \
-      using GeoW = ColGeom<T, (1 << LG), EP, CW>;                                                   \
-      if (n2 % GeoW::CC == 0) {                                                                     \
-        hipLaunchKernelGGL((k_fft_rows_t<T, (1 << LG), S, EP, CW, ROUT>), dim3(unsigned(n2 / GeoW::CC), unsigned(segs)), \
-                           dim3(GeoW::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2, \
-                           seg_stride, static_cast<const C*>(tw));                                  \
-        return true;                                                                                \
-      }                                                                                             \
-      using Geo = ColGeom<T, (1 << LG), EP>;                                                        \
+      using Geo = ColGeom<T, (1 << LG), EP, CW>;                                                    \
       if (n2 % Geo::CC) return false;                                                               \
-      hipLaunchKernelGGL((k_fft_rows_t<T, (1 << LG), S, EP, 0, ROUT>), dim3(unsigned(n2 / Geo::CC), unsigned(segs)), \
-                         dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2,  \
+      hipLaunchKernelGGL((k_fft_rows_t<T, (1 << LG), S, EP, CW, ROUT>), dim3(unsigned(n2 / Geo::CC), unsigned(segs)), \
+                         dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2, \
                          seg_stride, static_cast<const C*>(tw));                                    \
       return true;                                                                                  \
     }                                                                                               \
@@ -755,17 +745,10 @@ bool launch_spec_rows_twist(int log2l, const void* in, void* out, int64_t n2, in
 #define X(LG)                                                                                       \
   case LG:                                                                                          \
     if constexpr ((LG) <= (sizeof(T) == 4 ? kMaxLog2Col32 : kMaxLog2Col64)) {                       \
-      using GeoW = ColGeom<T, (1 << LG), kPass2E, kRowWide>;                                        \
-      if (n2 % GeoW::CC == 0) {                                                                     \
-        hipLaunchKernelGGL((k_spec_rows_twist<T, (1 << LG), kPass2E, kRowWide>), dim3(unsigned(n2 / GeoW::CC), unsigned(segs)), \
-                           dim3(GeoW::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2, \
-                           seg_stride, static_cast<const C*>(tw), tw2);                             \
-        return true;                                                                                \
-      }                                                                                             \
-      using Geo = ColGeom<T, (1 << LG), kPass2E>;                                                   \
+      using Geo = ColGeom<T, (1 << LG), kPass2E, kRowWide>;                                         \
       if (n2 % Geo::CC) return false;                                                               \
-      hipLaunchKernelGGL((k_spec_rows_twist<T, (1 << LG), kPass2E>), dim3(unsigned(n2 / Geo::CC), unsigned(segs)), \
-                         dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2,  \
+      hipLaunchKernelGGL((k_spec_rows_twist<T, (1 << LG), kPass2E, kRowWide>), dim3(unsigned(n2 / Geo::CC), unsigned(segs)), \
+                         dim3(Geo::NT), 0, st, static_cast<const C*>(in), static_cast<C*>(out), n2, \
                          seg_stride, static_cast<const C*>(tw), tw2);                               \
       return true;                                                                                  \
     }                                                                                               \
