@@ -62,6 +62,13 @@ template <> struct BufIO<double2> {
   }
 };
 
+template <> struct BufIO<float4> {
+  template <int AUX>
+  __device__ static __forceinline__ float4 load(rsrc_t r, uint32_t voff, uint32_t soff) {
+    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, AUX));
+  }
+};
+
 template <> struct BufIO<float> {
   template <int AUX>
   __device__ static __forceinline__ float load(rsrc_t r, uint32_t voff, uint32_t soff) {

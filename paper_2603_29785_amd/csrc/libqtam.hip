@@ -238,7 +238,7 @@ void twiddles_strided(std::vector<T>& out, int64_t count, int64_t step, int64_t 
 // thread, in the order the engine reads it (see BlockFft::tw_offset): for
 // each pass with stride ns > 1 and radix R, exp(-2 pi i r k / (ns R)),
 // k in [0, ns), for r = 1, 2, 4, 8 (< R) or for every r in [1, R), as
-// tw_full_pass(mode, ns) says.
+// tw_full_pass(mode, ns) says (those in pairs in FP32).
 template <typename T>
 void stockham_twiddles(std::vector<T>& out, int64_t L, int64_t e, int mode = TW_POW) {
   out.clear();
@@ -248,12 +248,21 @@ void stockham_twiddles(std::vector<T>& out, int64_t L, int64_t e, int mode = TW_
     const int64_t R = radix(ns);
     if (ns == 1) continue;
     const bool full = tw_full_pass(mode, static_cast<int>(ns));
-    for (int64_t r = 1; r < R; r = full ? r + 1 : 2 * r)
-      for (int64_t k = 0; k < ns; ++k) {
-        const double a = -2.0 * M_PI * static_cast<double>(r * k) / static_cast<double>(ns * R);
-        out.push_back(static_cast<T>(std::cos(a)));
-        out.push_back(static_cast<T>(std::sin(a)));
-      }
+    auto push = [&](int64_t r, int64_t k) {
+      const double a = -2.0 * M_PI * static_cast<double>(r * k) / static_cast<double>(ns * R);
+      out.push_back(static_cast<T>(std::cos(a)));
+      out.push_back(static_cast<T>(std::sin(a)));
+    };
+    if (full && tw_pairs<T>()) {
+      for (int64_t r = 1; r < R; r += 2)
+        for (int64_t k = 0; k < ns; ++k) {
+          push(r, k);
+          push(r + 1, k);
+        }
+    } else {
+      for (int64_t r = 1; r < R; r = full ? r + 1 : 2 * r)
+        for (int64_t k = 0; k < ns; ++k) push(r, k);
+    }
   }
   if (out.empty()) out.assign(2, T(0));
 }
