@@ -353,6 +353,9 @@ template <typename T>
 qtam_status upload(qtam_plan_s* pl) {
   HostPlan& hp = pl->hp;
   Blob blob;
+  // the six row tables and room for the rest: growing by doubling copies and
+  // faults in the whole blob again wherever a size crosses a power of two
+  blob.bytes.reserve(6 * (pl->bs_os ? 2 : 1) * sizeof(T) * size_t(hp.sum_len) + (size_t(4) << 20));
   std::vector<RowMeta> rm(hp.rows);
   for (int k = 0; k < hp.rows; ++k)
     rm[k] = RowMeta{hp.centre[k], hp.lo[k], hp.hi[k], static_cast<int>(hp.offset[k])};
