@@ -67,13 +67,17 @@ struct RowGeom {
 // 128 registers and the LDS of a CU hold twice the rows and more of them load,
 // store or transform at any time. It takes enough rows to fill the chip twice
 // over: with fewer, the one-group form has twice the waves per row. The
-// butterflies are the same in both, so are the results, bit for bit.
-// Measured (MI355X, forward / inverse rows, us, one group : two groups):
-//   FP32 N_out  4096, 65536 rows 537/603 : 499/587;   2048 rows 21/24 : 22/24
-//   FP32 N_out  8192, 16384 rows 343/395 : 291/329;    512 rows 16/19 : 17/18
-//   FP32 N_out 16384,  8192 rows 416/465 : 326/372;    256 rows 20/20 : 21/21
-//   FP64 N_out  4096, 16384 rows 276/314 : 239/279;    512 rows 15/15 : 16/16
-//   FP64 N_out  8192,  8192 rows 386/414 : 325/358;    256 rows 20/18 : 20/20
+// butterflies are the same in both, and row_stats adds up in one order, so are
+// all results, bit for bit.
+// Measured (MI355X, forward / inverse rows, us, one group : two groups; few rows
+// with products of twiddles in every pass):
+//   FP32 N_out  4096, 65536 rows 501/573 : 477/561;   2048 rows 21/24 : 22/24
+//   FP32 N_out  8192, 16384 rows 332/373 : 284/320;    512 rows 16/19 : 17/18
+//   FP32 N_out 16384,  8192 rows 388/438 : 314/356;    256 rows 20/20 : 21/21
+//   FP64 N_out  4096, 16384 rows 281/315 : 234/279;    512 rows 15/15 : 16/16
+//   FP64 N_out  8192,  8192 rows 385/412 : 323/361;    256 rows 20/18 : 20/20
+// (At its 128 registers k_inv_rows<double, 4096>, k_fwd_rows<float, 2048> and the
+// FP32 dense rows spill 8 to 24 bytes a lane in this form, and gain all the same.)
 template <typename T, int L> constexpr bool wide_rows() {
   return sizeof(T) == 4 ? L >= 2048 && L <= 16384 : L >= 1024 && L <= 8192;
 }

@@ -24,7 +24,10 @@
 // of a few KiB that stays in the L1 cache: each twiddle is then rounded once.
 // With products in that pass too a row's FP32 error is 5 to 7% larger and its
 // systematic part, a scale below 1, 34 to 52% (rel-L2 of 512 / 2048 / 4096
-// points 1.12e-7 / 1.26e-7 / 1.35e-7 against 1.04e-7 / 1.19e-7 / 1.29e-7).
+// points 1.12e-7 / 1.26e-7 / 1.35e-7 against 1.04e-7 / 1.19e-7 / 1.29e-7). As
+// fifteen 8-byte loads it costs 3 to 10% of the rows (4096 values 498/577 us
+// forward / inverse against 486/542), as eight 16-byte loads (FP32, tw_pairs)
+// next to nothing: 472/561.
 // Direction S = -1 computes sum_n a_n e^{-2 pi i nk/L}, S = +1 the
 // unnormalised inverse kernel e^{+2 pi i nk/L} (conjugated twiddles).
 // Arithmetic: twiddles and rotations are applied inside the butterflies' fused

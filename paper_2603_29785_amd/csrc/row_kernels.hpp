@@ -103,6 +103,8 @@ __global__ __launch_bounds__((RowsGeom<T, L, WIDE>::NT), (WIDE ? 4 : 1)) void k_
 // above, into the workspace), then k_fft_rows_t, which writes the interleaved
 // tile. blockIdx.y = row * R + n1. Measured, 64 rows, FP32, forward + dense:
 // 4 x 131072 samples (R = 1) 396 to 300 us, 4 x 98304 (R = 3) 433 to 255 us.
+// (4096-point columns of R = 3, 5, from 2^24-point rows on, spill 248 bytes a
+// lane; two rows of 3 2^24 samples 3.6 to 2.2 ms.)
 template <typename T, int L2, int R>
 __global__ __launch_bounds__((ColGeom<T, L2>::NT)) void k_dense_cols(
     const typename Complex<T>::type* __restrict__ Sbuf, typename Complex<T>::type* __restrict__ A,
@@ -665,9 +667,9 @@ __global__ __launch_bounds__((RowGeom<T, L>::NT)) void k_inv_rows_bs(
 // being hoisted out of the block loop (they would take 64 registers and spill).
 // Measured on MI355X, FP32, 62 rows of 24576-sample segments: forward + inverse
 // of 128 segments with N_out = 12289 (support 1537) 11.45 ms by length-32768
-// transforms through memory, 0.77 ms here (L = 4096, 4 or 5 blocks); forward of
+// transforms through memory, 0.74 ms here (L = 4096, 4 or 5 blocks); forward of
 // 1024 segments with N_out = 1028 (support 1027) 0.87 ms by one length-4096
-// convolution per row, 0.57 ms here (L = 2048, one block for rows of at most
+// convolution per row, 0.47 ms here (L = 2048, one block for rows of at most
 // 507 bins a side, else two). Rows whose convolution over all outputs is
 // shorter than one per wave (1024 values FP32, 512 FP64) keep that form: here
 // 8700 rows of 109 values, forward + inverse, took 69 us against 51.

@@ -330,7 +330,7 @@ __global__ __launch_bounds__(256) void k_radix_twist(const typename Complex<T>::
 // transform's latency at few. Measured on MI355X, FP32: spectra of 1024 x
 // 24576 samples (R = 3) 148 us as permutation, transforms, combination and
 // twist, 78 us here; one 16384-sample segment forward + inverse (R = 1) 35.9
-// to 33.1 us. Segments above one workgroup, without the permutation passes
+// to 32.3 us. Segments above one workgroup, without the permutation passes
 // (256 x 49152 samples, forward + inverse with 16 rows): 229 to 184 us.
 template <typename T, int M2, int R>
 struct SegGeom {
